@@ -160,7 +160,7 @@ const char* vrn_last_error(void);
 /* Validate a field -- the multiresolution hash grid of Sec. 4 (after iNGP),
  * the density and color MLPs of Sec. 6 and the binary occupancy grid of
  * Sec. 4.3 -- and copy it into library-owned device memory (tables as given,
- * occupancy bits plus a coarse block mip, MLP weights re-laid out for MFMA in
+ * occupancy bits plus the distances between non-empty bricks, MLP weights re-laid out for MFMA in
  * FP32, FP16 and BF16).  The field stays resident until unloaded. */
 vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* desc, vrn_field_id* out);
 
@@ -292,7 +292,7 @@ vrn_status vrn_prune_grid(vrn_ctx* ctx, vrn_field_id field, float alpha, uint32_
                           vrn_dtype compute, uint32_t* d_bits_out, float* d_max_opacity, void* hip_stream);
 
 /* Replace a resident field's occupancy grid (Sec. 4.3) with device bits (same layout as
- * vrn_field_desc.occ_bits), rebuilding its bricks and coarse grids on
+ * vrn_field_desc.occ_bits), rebuilding its bricks and their distances on
  * hip_stream.  Renders of this field on other streams must be ordered by
  * the caller. */
 vrn_status vrn_set_occupancy(vrn_ctx* ctx, vrn_field_id field, const uint32_t* d_bits, void* hip_stream);
@@ -434,7 +434,7 @@ double vrn_server_clock(void);
 
 /* Counters of a library built with -DVRN_DEBUG_CHECKS (synchronises the
  * device first): out[0] hash-table offsets outside their level, out[1]
- * brick and out[2] coarse-grid indices outside the grid, out[3] framebuffer
+ * brick indices outside the grid, out[2] unused (0), out[3] framebuffer
  * writes outside the frame, out[4] NaN encoded features, out[5] NaN MLP
  * outputs.  The kernels count instead of trapping.  reset != 0 zeroes the
  * counters after reading.  VRN_ERR_UNSUPPORTED in release builds. */

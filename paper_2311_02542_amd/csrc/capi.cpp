@@ -446,15 +446,10 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
   for (uint64_t i = 0; i < nw; ++i)
     if (!finite(d->weights[i])) return fail(VRN_ERR_INVALID_ARG, "MLP weights contain non-finite values");
 
-  // occupancy: 4x4x4 bricks (one 64-bit word each) and a coarse grid of
-  // <= 32^3 blocks (2^cshift cells, a multiple of the brick) for LDS
+  // occupancy: 4x4x4 bricks (one 64-bit word each)
   const uint32_t Gb = (G + 3) / 4;
-  uint32_t cshift = 2;
-  while (((G + (1u << cshift) - 1) >> cshift) > 32u) ++cshift;
-  const uint32_t Gc = (G + (1u << cshift) - 1) >> cshift;
   const uint64_t n_fine = (uint64_t)G * G * G, n_words = (n_fine + 31) / 32;
   std::vector<unsigned long long> bricks((size_t)Gb * Gb * Gb, 0ull);
-  std::vector<uint32_t> coarse(((uint64_t)Gc * Gc * Gc + 31) / 32, 0u);
   for (uint64_t w = 0; w < n_words; ++w) {
     uint32_t word = d->occ_bits[w];
     while (word) {
@@ -465,30 +460,8 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
       const uint32_t x = (uint32_t)(i % G), y = (uint32_t)((i / G) % G), z = (uint32_t)(i / ((uint64_t)G * G));
       const uint64_t bi = (x >> 2) + (uint64_t)Gb * ((y >> 2) + (uint64_t)Gb * (z >> 2));
       bricks[bi] |= 1ull << ((x & 3) + 4 * (y & 3) + 16 * (z & 3));
-      const uint64_t ci = (x >> cshift) + (uint64_t)Gc * ((y >> cshift) + (uint64_t)Gc * (z >> cshift));
-      coarse[ci >> 5] |= 1u << (ci & 31);
     }
   }
-  // the coarse grid dilated by one block: empty only where the block and all
-  // 26 neighbours are empty (long empty runs are walked block by block)
-  std::vector<uint32_t> coarse_dil(coarse.size(), 0u);
-  for (uint32_t cz = 0; cz < Gc; ++cz)
-    for (uint32_t cy = 0; cy < Gc; ++cy)
-      for (uint32_t cx = 0; cx < Gc; ++cx) {
-        bool any = false;
-        for (int dz = -1; dz <= 1 && !any; ++dz)
-          for (int dy = -1; dy <= 1 && !any; ++dy)
-            for (int dx = -1; dx <= 1 && !any; ++dx) {
-              const int x = (int)cx + dx, y = (int)cy + dy, z = (int)cz + dz;
-              if (x < 0 || y < 0 || z < 0 || x >= (int)Gc || y >= (int)Gc || z >= (int)Gc) continue;
-              const uint64_t ci = (uint64_t)x + (uint64_t)Gc * ((uint64_t)y + (uint64_t)Gc * (uint64_t)z);
-              any = (coarse[ci >> 5] >> (ci & 31)) & 1u;
-            }
-        if (any) {
-          const uint64_t ci = (uint64_t)cx + (uint64_t)Gc * ((uint64_t)cy + (uint64_t)Gc * (uint64_t)cz);
-          coarse_dil[ci >> 5] |= 1u << (ci & 31);
-        }
-      }
   std::vector<float> w32, bias;
   std::vector<uint16_t> w16, wbf, wx3;
   arrange_weights(d->weights, (int)L, (int)nsh, w32, w16, wbf, wx3, bias);
@@ -523,9 +496,9 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
     }
   }
   const uint64_t tab_bytes = n_tab * (d->table_dtype == VRN_F16 ? 2 : 4);
-  const uint64_t need = tab_bytes + bricks.size() * 8 + coarse.size() * 8 + (w32.size() + bias.size()) * 4 +
+  const uint64_t need = tab_bytes + bricks.size() * 8 + (w32.size() + bias.size()) * 4 +
                         (w16.size() + wbf.size() + wx3.size()) * 2 + lv.size() * sizeof(LevelDev) + lat.size() * 4 +
-                        bricks.size() * 4 + 256;
+                        bricks.size() * 5 + 256;
   if (ctx->budget && ctx->used + need > ctx->budget)
     return fail(VRN_ERR_BUDGET, "loading the field would exceed the HBM budget");
 
@@ -536,20 +509,19 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
   uint8_t* tab = nullptr;
   LevelDev* dlv = nullptr;
   unsigned long long* dbr = nullptr;
-  uint32_t *dco = nullptr, *dcd = nullptr;
   float *dw32 = nullptr, *dbias = nullptr, *dlat = nullptr;
   uint32_t *dlist = nullptr, *dcount = nullptr;
+  uint8_t* ddist = nullptr;
   const std::vector<uint32_t> zeros(64, 0u);
   uint16_t *dw16 = nullptr, *dwbf = nullptr, *dwx3 = nullptr;
   if ((e = upload(f, static_cast<const uint8_t*>(d->tables), tab_bytes, &tab)) ||
       (e = upload(f, lv.data(), lv.size(), &dlv)) || (e = upload(f, bricks.data(), bricks.size(), &dbr)) ||
-      (e = upload(f, coarse.data(), coarse.size(), &dco)) ||
-      (e = upload(f, coarse_dil.data(), coarse_dil.size(), &dcd)) || (e = upload(f, w32.data(), w32.size(), &dw32)) ||
+      (e = upload(f, w32.data(), w32.size(), &dw32)) ||
       (e = upload(f, w16.data(), w16.size(), &dw16)) || (e = upload(f, wbf.data(), wbf.size(), &dwbf)) ||
       (e = upload(f, wx3.data(), wx3.size(), &dwx3)) ||
       (e = upload(f, bias.data(), bias.size(), &dbias)) ||
       (use_table && (e = upload(f, lat.data(), lat.size(), &dlat))) ||
-      (e = alloc_only(f, bricks.size(), &dlist)) || (e = upload(f, zeros.data(), zeros.size(), &dcount)) ||
+      (e = alloc_only(f, bricks.size(), &ddist)) || (e = alloc_only(f, bricks.size(), &dlist)) || (e = upload(f, zeros.data(), zeros.size(), &dcount)) ||
       (e = hipEventCreateWithFlags(&f->noalloc_ev, hipEventDisableTiming))) {
     free_field(f);
     return e == hipErrorOutOfMemory ? fail(VRN_ERR_OUT_OF_MEMORY, "device allocation failed")
@@ -558,8 +530,7 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
   F.tables = tab;
   F.levels = dlv;
   F.bricks = dbr;
-  F.coarse = dco;
-  F.coarse_dil = dcd;
+  F.dist = ddist;
   F.brick_list = dlist;
   F.brick_count = dcount;
   F.w32 = dw32;
@@ -574,8 +545,6 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
   F.bmask = F.Tmask * (F.table_f16 ? 4u : 8u);
   F.G = G;
   F.Gb = Gb;
-  F.Gc = Gc;
-  F.cshift = cshift;
   F.nsh = nsh;
   for (int a = 0; a < 3; ++a) F.amin[a] = d->aabb_min[a];
   F.cs = (float)((double)G / (double)d->extent);
@@ -610,6 +579,19 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
     }
     F.lat_inv_log = (float)(1.0 / std::log1p((double)d->step_growth));
   }
+  // the most by which the shape's index of an entry exceeds the entry's own
+  // (the FP32 recurrence drifts from the shape on long tables), with room for
+  // the device's own rounding of the shape
+  F.lat_slack = 0.0f;
+  if (use_table) {
+    double over = 0.0;
+    for (uint32_t k = 0; k <= d->max_lattice && std::isfinite(lat[k]); ++k) {
+      const double kf = lat[k] < F.lat_tsw ? ((double)lat[k] - 0.5 * d->dt) / d->dt
+                                           : F.lat_ksw + std::log((double)lat[k] / F.lat_tsw) * F.lat_inv_log;
+      over = std::max(over, kf - k);
+    }
+    F.lat_slack = (float)over + 0x1p-20f * (float)d->max_lattice + 0.01f;
+  }
   F.contract = d->contraction;
   for (int a = 0; a < 3; ++a) F.center[a] = d->center[a];
   F.radius = d->contraction ? d->radius : 1.0f;
@@ -618,6 +600,10 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
   F.dense_mask = 0;
   for (uint32_t l = 0; l < L; ++l) F.dense_mask |= lv[l].dense << l;
   F.c1_ksteps = 8u;
+  if ((e = launch_brick_distance(F, nullptr)) != hipSuccess || (e = hipStreamSynchronize(nullptr)) != hipSuccess) {
+    free_field(f);
+    return hip_fail(e, "brick distances");
+  }
   const vrn_field_id id = ctx->next_id++;
   ctx->fields[id] = f;
   ctx->used += f->bytes;

@@ -39,8 +39,10 @@ struct Ray {
   float lr;      // ln(r) + ln(2 s / extent): log of the LOD footprint per unit t
   float delta;   // block-skip margin in cell units (bounds FP32 rounding of q)
   int k, k_hi;   // lattice cursor and last lattice index worth testing
-  int brick;     // index of the 4x4x4 brick whose bits are cached below (-1: none)
-  uint32_t blo, bhi;
+  int brick;     // index of the 4x4x4 brick cached below (-1: none)
+  int dist;      // its distance to the nearest non-empty brick (0: non-empty)
+  uint32_t blo, bhi;  // its bits, when it is non-empty
+  float iq[3];   // lattice steps (sample tables: ray parameter) per cell along each axis, finite
   float nx, ny, nz;  // right neighbour's direction (contracted LOD footprint)
 };
 
@@ -123,8 +125,12 @@ __device__ __forceinline__ void lattice_range(const FieldDev& F, Ray& r) {
   if (GEO == 1 && F.contract) {
     r.k = 0;
     r.k_hi = (int)F.lat_K - 1;
-    const float M = (fmaxf(fabsf(o[0] - F.center[0]), fmaxf(fabsf(o[1] - F.center[1]), fabsf(o[2] - F.center[2]))) +
-                     F.lat[F.lat_K - 1]) * F.inv_radius + 2.0f;
+    // Canonical u strays from the exact one by at most 2^-22 (|c| + |o - c| +
+    // t) / radius, with t <= sqrt(3) (|o - c| + m radius), and C shrinks that by
+    // 4 / m or more outside the unit ball: y by at most 2^-21 M, with
+    const float oc = fmaxf(fabsf(o[0] - F.center[0]), fmaxf(fabsf(o[1] - F.center[1]), fabsf(o[2] - F.center[2])));
+    const float ce = fmaxf(fabsf(F.center[0]), fmaxf(fabsf(F.center[1]), fabsf(F.center[2])));
+    const float M = (6.0f * oc + 2.0f * ce) * F.inv_radius + 6.0f;
     r.delta = ldexpf(F.cs * M + (float)F.G + 1.0f, -20);
     return;
   }
@@ -195,8 +201,16 @@ __device__ __forceinline__ void setup_ray(const FieldDev& F, const vrn_camera& c
     r.nz = d2[2];
   }
   r.brick = -1;
+  r.dist = 0;
   r.blo = r.bhi = 0u;
   lattice_range<GEO>(F, r);
+  // (hardware reciprocals: skip_straight's margin covers their ~1 ulp)
+  const float per = GEO == 0 ? F.cs * F.dt : (F.contract ? F.inv_radius * F.cs : F.cs);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float inv = __builtin_amdgcn_rcpf(d[a] * per);
+    r.iq[a] = copysignf(fminf(fabsf(inv), 1.0e30f), d[a]);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -264,8 +278,7 @@ __device__ __forceinline__ int cell_of(float q, int G) {
   return i;
 }
 
-// x + n (y + n z) for the coarse-block and brick grids (n <= 256, indices
-// below 2^24): 24-bit multiplies issue at the full rate, where a 32-bit
+// x + n (y + n z) for the brick grid (n <= 256, indices below 2^24): 24-bit multiplies issue at the full rate, where a 32-bit
 // multiply-add would take the quarter-rate 64-bit form.
 __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) {
   uint32_t d;
@@ -276,260 +289,116 @@ __device__ __forceinline__ uint32_t grid_index(uint32_t x, uint32_t y, uint32_t 
   return mad_u24(n, mad_u24(n, z, y), x);
 }
 
-__device__ __forceinline__ bool bit_set(const uint32_t* bits, uint32_t idx) {
-  return (bits[idx >> 5] >> (idx & 31u)) & 1u;
-}
-
-// Contracted fields, outside the unit L-inf ball: the canonical samples lie
-// on the image of the straight ray under C.  Over a stretch [t_a, t_b] on
-// which one axis i dominates u at both ends, with the same sign and
-// |u_i| > 1, it dominates throughout (|u_j| - |u_i| is convex in t and
-// |u_i| linear), so y_i = sign (2 - 1/|u_i|) is monotone, and y_j = a b with
-// a = 2 - 1/|u_i| in (1, 2) and b = u_j / |u_i| both monotone: the products
-// of their end values bound y_j.  CurveStart holds the start of a stretch
-// (sample r.k); curve_bound returns the box, in cell units, that holds the
-// curve from there to sample kb, or false when the dominance condition
-// fails.  Canonical sample positions lie within FP32 error (far below a
-// hundredth of a cell) of the curve.
-struct CurveStart {
-  float b[3], s, a;  // b = u / m at the start (the dominant axis' entry is unused)
-  int axis;
-};
-
-__device__ __forceinline__ void curve_u(const FieldDev& F, const Ray& r, float t, float u[3]) {
-  u[0] = (r.ox + t * r.dx - F.center[0]) * F.inv_radius;
-  u[1] = (r.oy + t * r.dy - F.center[1]) * F.inv_radius;
-  u[2] = (r.oz + t * r.dz - F.center[2]) * F.inv_radius;
-}
-
-__device__ __forceinline__ void curve_dominant(const float u[3], int& axis, float& m) {
-  const float ax = fabsf(u[0]), ay = fabsf(u[1]), az = fabsf(u[2]);
-  axis = (ax >= ay && ax >= az) ? 0 : (ay >= az ? 1 : 2);
-  m = fmaxf(ax, fmaxf(ay, az));
-}
-
-// False when sample r.k lies in the unit ball (no curve bound applies).
-__device__ __forceinline__ bool curve_start(const FieldDev& F, const Ray& r, CurveStart& c) {
-  float u[3], m;
-  curve_u(F, r, F.lat[r.k], u);
-  curve_dominant(u, c.axis, m);
-  c.s = c.axis == 0 ? u[0] : (c.axis == 1 ? u[1] : u[2]);
-  c.a = 2.0f - 1.0f / m;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) c.b[a] = a == c.axis ? 0.0f : u[a] / m;
-  return m > 1.0f;
-}
-
-__device__ __forceinline__ bool curve_bound(const FieldDev& F, const Ray& r, const CurveStart& c, int kb,
-                                            float qlo[3], float qhi[3]) {
-  const float g4 = 0.25f * (float)F.G;
-  float ub[3];
-  curve_u(F, r, F.lat[kb], ub);
-  int ib;
-  float mb;
-  curve_dominant(ub, ib, mb);
-  const float sb = ib == 0 ? ub[0] : (ib == 1 ? ub[1] : ub[2]);
-  if (ib != c.axis || (c.s > 0.0f) != (sb > 0.0f) || !(mb > 1.0f)) return false;
-  const float ab = 2.0f - 1.0f / mb;
-  const float alo = fminf(c.a, ab), ahi = fmaxf(c.a, ab);
+// Lattice steps (sample tables: ray parameter) from the current sample to the
+// exit of an empty box, less a margin; 0 where the sample is too near a face.
+// The box holds the sample's cell c (q its canonical position): an empty cell
+// of a non-empty brick alone, or the bricks nearer than dist to an empty one,
+// which hold no occupied cell (beyond the grid nothing is occupied).  Only
+// the faces towards which the ray moves matter.  Along an axis the exact ray
+// advances 1 / iq cells a step and canonical positions stray from it by at
+// most delta / 2, so of the samples up to the exit from the box shrunk by mu =
+// 2 delta none has a canonical cell beyond a far face: the second delta covers
+// the rounding of this evaluation, a few ulp of G.  None falls behind a near
+// face either when the sample lies delta or more inside its cell; within
+// delta of a face (one sample in a hundred) no skip is made.
+// face_lo and face_hi bound the faces (identity region of contracted fields).
+template <bool CLAMP>
+__device__ __forceinline__ float exit_steps(const Ray& r, const float q[3], const int c[3], float face_lo,
+                                            float face_hi) {
+  const bool full = r.dist != 0;       // empty brick
+  const int sh = full ? 2 : 0;
+  const int up = full ? r.dist : 1, dn = 1 - up;
+  const float d[3] = {r.dx, r.dy, r.dz};
+  float n[3], inside = 0.0f;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    float lo, hi;
-    if (a == c.axis) {
-      lo = c.s > 0.0f ? alo : -ahi;
-      hi = c.s > 0.0f ? ahi : -alo;
-    } else {
-      const float ba = c.b[a], bb = ub[a] / mb;
-      const float blo = fminf(ba, bb), bhi = fmaxf(ba, bb);
-      lo = fminf(fminf(alo * blo, alo * bhi), fminf(ahi * blo, ahi * bhi));
-      hi = fmaxf(fmaxf(alo * blo, alo * bhi), fmaxf(ahi * blo, ahi * bhi));
-    }
-    qlo[a] = (lo + 2.0f) * g4;
-    qhi[a] = (hi + 2.0f) * g4;
+    float face = (float)(((c[a] >> sh) + (d[a] > 0.0f ? up : dn)) << sh);
+    if constexpr (CLAMP) face = fminf(fmaxf(face, face_lo), face_hi);
+    n[a] = fmaf(fabsf(r.iq[a]), -2.0f * r.delta, (face - q[a]) * r.iq[a]);
+    inside = fmaxf(inside, fabsf(__builtin_amdgcn_fractf(q[a]) - 0.5f));
   }
-  return true;
+  const float m = fminf(n[0], fminf(n[1], n[2]));
+  return inside <= 0.5f - r.delta ? m : 0.0f;
 }
 
-// Jump past the lattice samples that stay inside the empty box of `size`
-// cells with corner o (cell units), shrunk by delta.  The jump is taken only
-// when the current sample (q) and the landing sample both lie in the shrunk
-// box: by convexity every lattice sample in between lies in it too, and
-// delta >= twice the FP32 error of q, so no sample whose canonical cell is
-// occupied is ever passed.  Beyond the unit ball of a contracted field the
-// samples follow a curve: there a doubling search takes the farthest
-// r.k + 2^j (j >= 1) whose curve box, padded by a hundredth of a cell, lies
-// in the shrunk box.  Returns true if r.k moved.
-template <int GEO>
-__device__ __forceinline__ bool skip_box(const FieldDev& F, Ray& r, const float q[3], int ox, int oy, int oz,
-                                         float size, float& t_land) {
-  const float lo[3] = {ox * size + r.delta, oy * size + r.delta, oz * size + r.delta};
-  const float hi[3] = {(ox + 1) * size - r.delta, (oy + 1) * size - r.delta, (oz + 1) * size - r.delta};
-  if (!(q[0] >= lo[0] && q[0] <= hi[0] && q[1] >= lo[1] && q[1] <= hi[1] && q[2] >= lo[2] && q[2] <= hi[2]))
-    return false;
-  if (GEO == 1 && F.contract) {
-    // only boxes inside the identity region (|u|inf <= 1: q in [G/4, 3G/4])
-    // map straight segments to straight segments
-    const float a = 0.25f * (float)F.G, b = 0.75f * (float)F.G;
-    if (!(ox * size >= a && oy * size >= a && oz * size >= a && (ox + 1) * size <= b && (oy + 1) * size <= b &&
-          (oz + 1) * size <= b)) {
-      CurveStart c;
-      if (!curve_start(F, r, c)) return false;
-      int best = r.k;
-      for (int step = 2; step < (1 << 20); step *= 2) {
-        const int kb = min(r.k + step, r.k_hi);
-        if (kb <= best) break;
-        float ql[3], qh[3];
-        if (!curve_bound(F, r, c, kb, ql, qh)) break;
-        if (!(ql[0] - 0.01f >= lo[0] && qh[0] + 0.01f <= hi[0] && ql[1] - 0.01f >= lo[1] && qh[1] + 0.01f <= hi[1] &&
-              ql[2] - 0.01f >= lo[2] && qh[2] + 0.01f <= hi[2]))
-          break;
-        best = kb;
-        if (kb == r.k_hi) break;
-      }
-      if (best < r.k + 2) return false;
-      r.k = best + 1;
-      return true;
-    }
-  }
-  // approximate exit parameter (reciprocals need not be exact: the landing
-  // sample is re-tested with the canonical arithmetic below)
+// Largest index whose table entry is certainly <= t (-1: none is certain):
+// the table's shape as in table_count_le, less the most by which an entry's
+// shape index exceeds its own (lat_slack, found on the host).
+__device__ __forceinline__ int table_floor(const FieldDev& F, float t) {
+  const float kf = t < F.lat_tsw ? (t - 0.5f * F.dt) * F.inv_dt
+                                 : F.lat_ksw + __logf(t / F.lat_tsw) * F.lat_inv_log;
+  return (int)fminf(fmaxf(floorf(kf - F.lat_slack), -1.0f), (float)(F.lat_K - 1u));
+}
+
+// Beyond the unit ball of a contracted field the samples follow the image of
+// the straight ray under C.  A stretch of ray parameter after t over which
+// the image stays in the empty box of exit_steps, less a margin; <= 0: none.
+// With u = (x - center) / radius, v = du/dt, m = |u|inf on axis i, s =
+// sign(u_i), m' = s v_i, r = u / m and w = v - r m': y_i = s (2 - 1/m) moves
+// at m' / m^2, and y_j = (2 - 1/m) r_j, as r_j' = w_j / m, at no more than
+// |m'| / m^2 + (2 - 1/m) / m |w_j|, while w_j' = -w_j m' / m.  For an outward
+// ray (m' >= 0) all of these fall as m grows, so their values at t bound them
+// for as long as axis i dominates.  An inward one is followed to the middle
+// between m and 1, where m is replaced by that value ml and w_j by w_j m / ml.
+// Axis j cannot take over before (m - |u_j|) / (|v_j| - m').  (A box bound of
+// the curve searched by doubling stretches took 3 to 4 times the tests.)
+__device__ __forceinline__ float exit_curved(const FieldDev& F, const Ray& r, float t, const float q[3],
+                                             const int c[3]) {
   const float o[3] = {r.ox, r.oy, r.oz};
   const float d[3] = {r.dx, r.dy, r.dz};
-  float te = 3.0e38f;
+  float u[3], v[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const float bq = signbit(d[a]) ? lo[a] : hi[a];
-    float xb = bq * F.inv_cs + F.amin[a];
-    if (GEO == 1 && F.contract) xb = xb * F.radius + F.center[a];
-    te = fminf(te, (xb - o[a]) * __builtin_amdgcn_rcpf(d[a]));
+    u[a] = (fmaf(t, d[a], o[a]) - F.center[a]) * F.inv_radius;
+    v[a] = d[a] * F.inv_radius;
   }
-  int kb;
-  if constexpr (GEO == 0) {
-    const float kbf = fminf(floorf(te * F.inv_dt - 0.5f), (float)r.k_hi);
-    if (!(kbf >= (float)r.k + 2.0f)) return false;
-    kb = (int)kbf;
-  } else {
-    kb = min(table_count_le(F, te) - 1, r.k_hi);
-    if (kb < r.k + 2) return false;
-  }
-#pragma unroll
-  for (int tries = 0; tries < 2; ++tries, --kb) {
-    float t2, x2[3], q2[3];
-    lattice_q<GEO>(F, r, kb, t2, x2, q2);
-    if (q2[0] >= lo[0] && q2[0] <= hi[0] && q2[1] >= lo[1] && q2[1] <= hi[1] && q2[2] >= lo[2] &&
-        q2[2] <= hi[2]) {
-      r.k = kb + 1;
-      t_land = t2;
-      return true;
-    }
-  }
-  return false;
-}
-
-// Walk the coarse grid from block (bx, by, bz) along a straight ray through
-// consecutive blocks whose dilated bit is clear (the block and its 26
-// neighbours hold no occupied cell) and lie in [blo, bhi] on every axis,
-// and return the ray parameter where the walk leaves the last such block.
-// The ray in cell units is qo + t dq.  Every point within one block width of
-// a clear block lies in an empty block.  The walk and the canonical sample
-// positions both deviate from the exact ray by far less than a block, so
-// every lattice sample with t up to the returned value (rounded either way)
-// has an empty cell.
-__device__ __forceinline__ float coarse_run(const FieldDev& F, const uint32_t* dil, const float qo[3],
-                                            const float dq[3], int bx, int by, int bz, int blo, int bhi) {
-  const float cb = (float)(1u << F.cshift);
-  const int Gc = (int)F.Gc;
-  const int b0[3] = {bx, by, bz};
-  float tm[3], td[3];
-  int st[3];
+  const float m = fmaxf(fabsf(u[0]), fmaxf(fabsf(u[1]), fabsf(u[2])));
+  const int axis = fabsf(u[0]) == m ? 0 : (fabsf(u[1]) == m ? 1 : 2);
+  const float ui = axis == 0 ? u[0] : (axis == 1 ? u[1] : u[2]);
+  const float vi = axis == 0 ? v[0] : (axis == 1 ? v[1] : v[2]);
+  const float dm = ui > 0.0f ? vi : -vi;
+  const float ml = dm >= 0.0f ? m : 0.5f * (m + 1.0f);
+  const float im = __builtin_amdgcn_rcpf(m), il = __builtin_amdgcn_rcpf(ml);
+  const float base = fabsf(dm) * il * il, lat = (2.0f - il) * il * (m * il);
+  float n = dm >= 0.0f ? 3.0e38f : (m - ml) * __builtin_amdgcn_rcpf(-dm);
+  const bool full = r.dist != 0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const float inv = __builtin_amdgcn_rcpf(dq[a]);
-    st[a] = dq[a] > 0.0f ? 1 : (dq[a] < 0.0f ? -1 : 0);
-    tm[a] = st[a] == 0 ? 3.0e38f : ((float)(b0[a] + (st[a] > 0)) * cb - qo[a]) * inv;
-    td[a] = st[a] == 0 ? 3.0e38f : cb * fabsf(inv);
+    const float lo = (float)(full ? ((c[a] >> 2) + 1 - r.dist) * 4 : c[a]);
+    const float hi = (float)(full ? ((c[a] >> 2) + r.dist) * 4 : c[a] + 1);
+    const float room = fminf(q[a] - lo, hi - q[a]) - 2.0f * r.delta;
+    const float w = fabsf(v[a] - (u[a] * im) * dm);
+    n = fminf(n, room * __builtin_amdgcn_rcpf(fmaf(lat, w, base) * F.cs));
+    const float gain = fabsf(v[a]) - dm;
+    if (a != axis && gain > 0.0f) n = fminf(n, (m - fabsf(u[a])) * __builtin_amdgcn_rcpf(gain));
   }
-  int x = bx, y = by, z = bz;
-  float tx = tm[0], ty = tm[1], tz = tm[2];
-  float t_exit = 0.0f;
-  for (int it = 0; it < 3 * Gc; ++it) {
-    const bool ax = tx <= ty && tx <= tz;
-    const bool ay = !ax && ty <= tz;
-    const bool az = !ax && !ay;
-    t_exit = ax ? tx : (ay ? ty : tz);
-    x += ax ? st[0] : 0;
-    y += ay ? st[1] : 0;
-    z += az ? st[2] : 0;
-    if (x < blo || y < blo || z < blo || x > bhi || y > bhi || z > bhi) break;
-    if (bit_set(dil, grid_index((uint32_t)x, (uint32_t)y, (uint32_t)z, (uint32_t)Gc))) break;
-    tx += ax ? td[0] : 0.0f;
-    ty += ay ? td[1] : 0.0f;
-    tz += az ? td[2] : 0.0f;
-  }
-  return t_exit;
-}
-
-// When every coarse block touched by the curve's box from r.k to a sample
-// (padded by a hundredth of a cell) is clear, every sample of that stretch
-// has an empty cell.  A doubling search returns the farthest lattice index
-// r.k + 2^j whose stretch from r.k passes (r.k itself when none does).
-__device__ __forceinline__ int contracted_run(const FieldDev& F, const uint32_t* dil, const Ray& r) {
-  const float inv_cb = 1.0f / (float)(1u << F.cshift);
-  const int Gc = (int)F.Gc;
-  CurveStart c;
-  if (!curve_start(F, r, c)) return r.k;
-  // does the stretch [r.k, kb] stay in clear blocks?
-  auto stretch_clear = [&](int kb) -> bool {
-    float ql[3], qh[3];
-    if (!curve_bound(F, r, c, kb, ql, qh)) return false;
-    int b0[3], b1[3];
-    bool fits = true;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      b0[a] = (int)floorf((ql[a] - 0.01f) * inv_cb);
-      b1[a] = (int)floorf((qh[a] + 0.01f) * inv_cb);
-      fits = fits && b0[a] >= 0 && b1[a] < Gc && b1[a] - b0[a] <= 1;
-    }
-    if (!fits) return false;
-    bool clear = true;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int x = b0[0] + (k & 1), y = b0[1] + ((k >> 1) & 1), z = b0[2] + (k >> 2);
-      if (x <= b1[0] && y <= b1[1] && z <= b1[2])
-        clear = clear && !bit_set(dil, grid_index((uint32_t)x, (uint32_t)y, (uint32_t)z, (uint32_t)Gc));
-    }
-    return clear;
-  };
-  // gallop: double the stretch while it stays clear (a finer search past the
-  // first failure costs more probes than it saves lattice tests)
-  int best = r.k;
-  for (int step = 1; step < (1 << 20); step *= 2) {
-    const int kb = min(r.k + step, r.k_hi);
-    if (kb <= best || !stretch_clear(kb)) break;
-    best = kb;
-    if (kb == r.k_hi) break;
-  }
-  return best;
+  return n * (1.0f - 0x1p-16f);   // covers this evaluation's relative error
 }
 
 // Advance to the next evaluated sample within `budget` lattice tests.
 // Returns 1 (sample found; st, sx are its canonical t and x), 0 (budget used
-// up) or 2 (ray exhausted).  Occupancy is tested hierarchically: the coarse
-// grid (blocks of 2^cshift cells, in LDS), then the 4x4x4 brick (one 64-bit
-// load, kept in registers while the ray stays in the brick), then the cell
-// bit.  A sample in a clear block (dilated bit 0) jumps to the end of the
-// run of clear blocks: along the straight ray for bounded fields and inside
-// the unit ball of contracted ones (coarse_run), along bounds of the curved
-// image beyond it (contracted_run).  Other empty coarse blocks and empty
-// bricks are skipped with skip_box.  `coarse` holds the coarse grid and,
-// kCoarseWords later, its dilation.
+// up) or 2 (ray exhausted).  A test looks up the sample's 4x4x4 brick (kept in
+// registers while the ray stays in it): its distance in bricks to the nearest
+// non-empty one and, when that is 0, its 64 cell bits.  Every failed test then
+// skips: past the empty cell, or past all bricks nearer than the distance.
+// The skip is one formula without branches or a second look at the lattice
+// (exit_steps), so it pays even for a cell that holds a single further sample.
+// Bound by VALU issue and the latency of the chain from test to test: before,
+// a coarse grid in LDS with walks of its clear runs and single-box skips,
+// each re-testing where it landed, took 20.1 tests a ray on the stereo 2x2048^2
+// house frame (16-bit paths 2.87 ms) and 28 within the unbounded scene's room
+// (2.35-4.0 ms by pose); this takes 13.4 (2.48 ms) and 9.5 (1.27-1.86 ms).
+// Both loads are issued at once: the bits only after a distance of 0 ran
+// 0.8 % slower on the house frame.
+// Beyond the unit ball of a contracted field samples follow a curve, along
+// which exit_curved bounds the stretch that stays in the same empty box.
 template <int GEO>
-__device__ __forceinline__ int march_next(const FieldDev& F, const uint32_t* coarse, Ray& r, uint32_t budget,
-                                          uint32_t& steps, float& st, float sx[3]) {
+__device__ __forceinline__ int march_next(const FieldDev& F, Ray& r, uint32_t budget, uint32_t& steps,
+                                          float& st, float sx[3]) {
   const int G = (int)F.G;
   // sample-table lattices: the parameter of sample r.k is carried from the
   // previous test (tk, valid while kt == r.k) by the table's own
-  // recurrence, so stepping and box skips read no table entry
+  // recurrence, so stepping reads no table entry
   int kt = -1;
   float tk = 0.0f;
   for (uint32_t it = 0; it < budget; ++it) {
@@ -542,102 +411,52 @@ __device__ __forceinline__ int march_next(const FieldDev& F, const uint32_t* coa
       t = kt == r.k ? tk : F.lat[r.k];
       lattice_pos<GEO>(F, r, t, x, q);
     }
-    const int cx = cell_of(q[0], G), cy = cell_of(q[1], G), cz = cell_of(q[2], G);
-    // empty box to try to jump over: the cell's block of 2^bsh cells (-1: none)
-    int bsh = -1;
-    if ((unsigned)cx < (unsigned)G && (unsigned)cy < (unsigned)G && (unsigned)cz < (unsigned)G) {
-      const int bx = cx >> F.cshift, by = cy >> F.cshift, bz = cz >> F.cshift;
-      const uint32_t ci = grid_index((uint32_t)bx, (uint32_t)by, (uint32_t)bz, F.Gc);
-      VRN_DEBUG_COUNT(ci >= F.Gc * F.Gc * F.Gc, kDbgCoarse);
-      if (!bit_set(coarse, ci)) {
-        if (!bit_set(coarse + kCoarseWords, ci)) {
-          // a clear block starts a run of empty blocks: jump to its end
-          int kb = r.k;
-          // straight walks: bounded fields, and blocks wholly inside the unit
-          // ball of contracted ones (q in [G/4, 3G/4], where C is the
-          // identity); beyond it the curved image of the ray is bounded
-          // piecewise (contracted_run)
-          float qo[3], dq[3];
-          int blo = 0, bhi = (int)F.Gc - 1;
-          bool walk = true;
-          if (GEO == 1 && F.contract) {
-            const int ilo = (int)(F.G >> (2 + F.cshift)), ihi = (int)((3 * F.G) >> (2 + F.cshift)) - 1;
-            walk = bx >= ilo && by >= ilo && bz >= ilo && bx <= ihi && by <= ihi && bz <= ihi &&
-                   (ilo << F.cshift) == (int)(F.G >> 2) && ((ihi + 1) << F.cshift) == (int)((3 * F.G) >> 2);
-            blo = ilo;
-            bhi = ihi;
-            const float s = F.inv_radius * 0.25f * (float)F.G;
-            qo[0] = (r.ox - F.center[0]) * s + 0.5f * (float)F.G;
-            qo[1] = (r.oy - F.center[1]) * s + 0.5f * (float)F.G;
-            qo[2] = (r.oz - F.center[2]) * s + 0.5f * (float)F.G;
-            dq[0] = r.dx * s;
-            dq[1] = r.dy * s;
-            dq[2] = r.dz * s;
-          } else {
-            qo[0] = (r.ox - F.amin[0]) * F.cs;
-            qo[1] = (r.oy - F.amin[1]) * F.cs;
-            qo[2] = (r.oz - F.amin[2]) * F.cs;
-            dq[0] = r.dx * F.cs;
-            dq[1] = r.dy * F.cs;
-            dq[2] = r.dz * F.cs;
-          }
-          if (walk) {
-            const float te = coarse_run(F, coarse + kCoarseWords, qo, dq, bx, by, bz, blo, bhi);
-            if constexpr (GEO == 0) kb = (int)fminf(floorf(te * F.inv_dt - 0.5f), (float)r.k_hi);
-            else kb = min(table_count_le(F, te) - 1, r.k_hi);
-          } else if (GEO == 1 && F.contract) {
-            kb = contracted_run(F, coarse + kCoarseWords, r);
-          }
-          if (kb > r.k) {
-            r.k = kb + 1;
-            continue;
-          }
-        }
-        bsh = (int)F.cshift;
-      } else {
-        const int kx = cx >> 2, ky = cy >> 2, kz = cz >> 2;
-        const int brick = (int)grid_index((uint32_t)kx, (uint32_t)ky, (uint32_t)kz, F.Gb);
-        if (brick != r.brick) {
-          VRN_DEBUG_COUNT((uint32_t)brick >= F.Gb * F.Gb * F.Gb, kDbgBrick);
-          const unsigned long long b = F.bricks[brick];
-          r.brick = brick;
-          r.blo = (uint32_t)b;
-          r.bhi = (uint32_t)(b >> 32);
-        }
-        if ((r.blo | r.bhi) == 0u) {
-          bsh = 2;
-        } else {
-          const uint32_t bit = (uint32_t)((cx & 3) | ((cy & 3) << 2) | ((cz & 3) << 4));
-          const unsigned long long bits = ((unsigned long long)r.bhi << 32) | r.blo;
-          if ((bits >> bit) & 1ull) {
-            st = t;
-            sx[0] = x[0];
-            sx[1] = x[1];
-            sx[2] = x[2];
-            r.k++;
-            return 1;
-          }
-        }
-      }
+    const int c[3] = {cell_of(q[0], G), cell_of(q[1], G), cell_of(q[2], G)};
+    const bool inside = max(max((uint32_t)c[0], (uint32_t)c[1]), (uint32_t)c[2]) < (uint32_t)G;
+    int next = r.k + 1;
+    const int brick = (int)grid_index((uint32_t)c[0] >> 2, (uint32_t)c[1] >> 2, (uint32_t)c[2] >> 2, F.Gb);
+    if (inside && brick != r.brick) {
+      VRN_DEBUG_COUNT((uint32_t)brick >= F.Gb * F.Gb * F.Gb, kDbgBrick);
+      r.brick = brick;
+      const unsigned long long b = F.bricks[brick];
+      r.dist = F.dist[brick];
+      r.blo = (uint32_t)b;
+      r.bhi = (uint32_t)(b >> 32);
     }
-    float t_land = 0.0f;   // table entries are > 0: 0 means not known
-    const bool moved =
-        bsh >= 0 && skip_box<GEO>(F, r, q, cx >> bsh, cy >> bsh, cz >> bsh, (float)(1 << bsh), t_land);
+    const uint32_t bit = (uint32_t)((c[0] & 3) | ((c[1] & 3) << 2) | ((c[2] & 3) << 4));
+    const unsigned long long bits = ((unsigned long long)r.bhi << 32) | r.blo;
+    if (inside && r.dist == 0 && ((bits >> bit) & 1ull)) {
+      st = t;
+      sx[0] = x[0];
+      sx[1] = x[1];
+      sx[2] = x[2];
+      r.k++;
+      return 1;
+    }
+    if constexpr (GEO == 0) {
+      const float n = exit_steps<false>(r, q, c, 0.0f, 0.0f);
+      next += (int)__builtin_amdgcn_fmed3f(inside ? n : 0.0f, 0.0f, 16777216.0f);
+    } else if (inside) {
+      // inside the unit ball (q in [G/4, 3G/4]) C is the identity
+      const float lo = 0.25f * (float)F.G, hi = 0.75f * (float)F.G;
+      float n;
+      if (!F.contract) n = exit_steps<false>(r, q, c, 0.0f, 0.0f);
+      else if (fminf(q[0], fminf(q[1], q[2])) >= lo && fmaxf(q[0], fmaxf(q[1], q[2])) <= hi)
+        n = exit_steps<true>(r, q, c, lo, hi);
+      else n = exit_curved(F, r, t, q, c);
+      // (the exit's rounding, an ulp of t, is far inside the margin)
+      if (n > 0.0f) next = max(next, min(table_floor(F, t + n), r.k_hi) + 1);
+    }
     if constexpr (GEO == 1) {
-      // the next test's parameter: the successor of this one, or of the
-      // landing sample of a straight skip (r.k is then already past it);
-      // after a curve skip the next test reads the table
-      if (!moved) {
+      // the next test's parameter, when it is this one's successor
+      if (next == r.k + 1) {
         tk = table_next(F, t);
-        kt = r.k + 1;
-      } else if (t_land > 0.0f) {
-        tk = table_next(F, t_land);
-        kt = r.k;
+        kt = next;
       } else {
         kt = -1;
       }
     }
-    if (!moved) r.k++;
+    r.k = next;
   }
   return 0;
 }

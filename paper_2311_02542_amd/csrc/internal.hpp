@@ -20,7 +20,6 @@ constexpr int kBlock = 256;         // threads per render block (4 waves)
 constexpr int kBlockF32 = 1024;
 inline int render_block_threads(int compute) { return (compute == 0 || compute == 3) ? kBlockF32 : kBlock; }
 constexpr int kHidden = 64;
-constexpr int kCoarseWords = 1024;  // <= 32^3 bits of coarse occupancy in LDS
 constexpr int kMlpBatch = 1;        // 16-sample tiles per 16-bit MLP call (weights read once per call)
 
 // MFMA fragment layout of the MLP weights (see mlp_tile in device.hpp).
@@ -49,9 +48,8 @@ struct FieldDev {
   const void* tables;        // [L][T][2] fp32 or fp16
   const LevelDev* levels;    // [L]
   const unsigned long long* bricks;  // Gb^3 bricks of 4x4x4 cells, bit (x&3) + 4 (y&3) + 16 (z&3)
-  const uint32_t* coarse;    // Gc^3 bits (Gc <= 32), block = 2^cshift cells; staged in LDS
-  const uint32_t* coarse_dil;  // Gc^3 bits: 1 if the block or one of its 26 neighbours has an
-                               // occupied cell; staged in LDS after the coarse grid
+  const uint8_t* dist;       // [Gb^3] bricks to the nearest non-empty one (Chebyshev; 0: non-empty;
+                             // at most 255, which also stands for none)
   const float* w32;          // kW32Total
   const uint16_t* w16;       // kW16Total fp16 bits
   const uint16_t* wbf;       // kW16Total bf16 bits
@@ -59,7 +57,7 @@ struct FieldDev {
   const float* bias;         // kBiasTotal
   uint32_t L, log2T, Tmask, table_f16;
   uint32_t bmask;            // Tmask times the entry size in bytes (hash mask on byte offsets)
-  uint32_t G, Gb, Gc, cshift, nsh;
+  uint32_t G, Gb, nsh;
   float amin[3], cs;         // cs = fp32(G / extent)
   float dt, t_min, extent, inv_ln_f;
   float inv_dt, inv_cs;      // approximate reciprocals for skip estimates
@@ -75,13 +73,15 @@ struct FieldDev {
   float lat_tsw;             // first table entry whose step is the growth term (inf: none)
   float lat_ksw;             // its index
   float lat_inv_log;         // 1 / ln(1 + step_growth)
+  float lat_slack;           // the most by which an entry's index by that shape exceeds its own
   int32_t contract;          // L-infinity contraction on
   float center[3], inv_radius, radius;
   float lod_c2;              // ln(2 s): LOD constant when the footprint is already normalised
   uint32_t d1_ksteps;        // FP32 k-steps of the first density layer
   uint32_t c1_ksteps;        // FP32 k-steps of the first color layer
   // grid pruning: the non-empty bricks, listed on the device by each
-  // vrn_prune_grid call ([Gb^3] entries, count in its own 256-byte block)
+  // vrn_prune_grid call ([Gb^3] entries, count in its own 256-byte block);
+  // between its uses scratch of the distance build
   uint32_t* brick_list;
   uint32_t* brick_count;
 };
@@ -111,11 +111,10 @@ struct RenderArgs {
 
 // launchers (kernels.hip)
 // Debug builds (-DVRN_DEBUG_CHECKS) count, instead of trapping on, hash-table
-// offsets outside their level, brick and coarse-grid indices outside the
-// grid, framebuffer writes outside the frame and NaN features or MLP
+// offsets outside their level, brick indices outside the grid, framebuffer writes outside the frame and NaN features or MLP
 // outputs; vrn_debug_counters reads the counts.  Release builds compile none
 // of it.
-enum DebugSlot { kDbgTableOffset = 0, kDbgBrick, kDbgCoarse, kDbgPixel, kDbgFeature, kDbgMlpNaN, kDbgSlots };
+enum DebugSlot { kDbgTableOffset = 0, kDbgBrick, kDbgUnused, kDbgPixel, kDbgFeature, kDbgMlpNaN, kDbgSlots };
 #ifdef VRN_DEBUG_CHECKS
 extern __device__ unsigned long long vrn_debug_counts[kDbgSlots];
 #define VRN_DEBUG_COUNT(cond, slot)                                 \
@@ -153,6 +152,8 @@ hipError_t launch_encode(const FieldDev& F, const float* xyz, const float* t, co
 hipError_t launch_prune(const FieldDev& F, float alpha, uint32_t npts, int compute, uint32_t* bits_out,
                         float* max_op, int n_cu, hipStream_t s);
 hipError_t launch_set_occupancy(const FieldDev& F, const uint32_t* bits, hipStream_t s);
+// The distance grid of the field's bricks (F.dist), with F.brick_list as scratch.
+hipError_t launch_brick_distance(const FieldDev& F, hipStream_t s);
 hipError_t launch_mlp(const FieldDev& F, const float* feat, const float* dir, uint32_t n,
                       int compute, float* sigma, float* rgb, hipStream_t s);
 

@@ -7,7 +7,7 @@
 //      tiles (XCD-aware: block b works the image slice of XCD b % 8 first,
 //      so each XCD's L2 sees one coherent region of the frame);
 //   2. marches every ray to its next occupied lattice sample (bounded
-//      number of lattice tests per round, coarse empty blocks skipped);
+//      number of lattice tests per round, empty bricks skipped);
 //   3. compacts the lanes that found a sample into 16-sample tiles and, per
 //      tile, encodes the hash grid (4 lanes per sample, levels interleaved
 //      so LOD-skipped fine levels idle all lane groups equally) and runs the
@@ -121,16 +121,6 @@ __device__ __forceinline__ void run_mlp(const uint8_t* s_w, const float* s_b, co
                            o0, lg);
 }
 
-// Stage the coarse occupancy grid and its dilation into LDS ([kCoarseWords]
-// words each).
-__device__ __forceinline__ void load_coarse(const FieldDev& F, uint32_t* s_coarse) {
-  const uint32_t words = (F.Gc * F.Gc * F.Gc + 31u) / 32u;
-  for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) {
-    s_coarse[i] = F.coarse[i];
-    s_coarse[kCoarseWords + i] = F.coarse_dil[i];
-  }
-}
-
 // The lane that owns compacted sample s = 16 t + (lane & 15), from the
 // wave's slot table in LDS.
 __device__ __forceinline__ int tile_source(const uint32_t* s_slot_w, int ns, int t, int lane, bool& act) {
@@ -193,7 +183,6 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   __shared__ __align__(16) uint8_t s_w[WeightSmem<MODE>::kBytes];
   __shared__ float s_b[kBiasTotal];
   __shared__ LevelDev s_lv[kMaxLevels];
-  __shared__ uint32_t s_coarse[2 * kCoarseWords];
   __shared__ uint32_t s_off[kMaxCams + 1];
   __shared__ uint32_t s_rb[kMaxCams], s_re[kMaxCams];
   __shared__ uint32_t s_stats[6];
@@ -206,7 +195,6 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   const FieldDev& F = A.F;
   const __amdgpu_buffer_rsrc_t tab = table_rsrc(F);
   load_weights<MODE>(F, s_w, s_b);
-  load_coarse(F, s_coarse);
   if (threadIdx.x < F.L) s_lv[threadIdx.x] = F.levels[threadIdx.x];
   if (threadIdx.x < 6) s_stats[threadIdx.x] = 0;
   const uint32_t tx = (A.W + kTile - 1) / kTile;
@@ -237,8 +225,10 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   r.k_hi = -1;
   r.lr = 0.0f;
   r.brick = -1;
+  r.dist = 0;
   r.blo = r.bhi = 0u;
   r.delta = 0.0f;
+  r.iq[0] = r.iq[1] = r.iq[2] = 0.0f;
   r.ox = r.oy = r.oz = r.dx = r.dy = r.dz = 0.0f;
   uint32_t pix = kNone, n = 0;
   float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
@@ -319,7 +309,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     int mres = 0;
     float st = 0.0f, sx[3] = {0.0f, 0.0f, 0.0f}, slst = 0.0f, sdt = F.dt;
     if (pix != kNone) {
-      mres = march_next<GEO>(F, s_coarse, r, A.budget, st_steps, st, sx);
+      mres = march_next<GEO>(F, r, A.budget, st_steps, st, sx);
       if (mres == 2) retire();
       if (mres == 1) {
         if (F.lod) slst = (GEO == 1 && F.contract) ? level_star_contracted(F, r, st, sx) : level_star(F, st, r.lr);
@@ -492,9 +482,6 @@ __global__ void rays_kernel(const vrn_camera* cams, uint32_t n_cams, uint32_t W,
 template <int GEO>
 __global__ void march_kernel(FieldDev F, const vrn_camera* cams, uint32_t n_cams, uint32_t W, uint32_t H,
                              uint32_t* klist, uint32_t max_k, uint32_t* count) {
-  __shared__ uint32_t s_coarse[2 * kCoarseWords];
-  load_coarse(F, s_coarse);
-  __syncthreads();
   const uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
   if (i >= (uint64_t)n_cams * W * H) return;
   const uint32_t c = (uint32_t)(i / ((uint64_t)W * H));
@@ -504,7 +491,7 @@ __global__ void march_kernel(FieldDev F, const vrn_camera* cams, uint32_t n_cams
   uint32_t cnt = 0, steps = 0;
   float st, sx[3];
   while (cnt < F.max_samples) {
-    if (march_next<GEO>(F, s_coarse, r, 0x40000000u, steps, st, sx) != 1) break;
+    if (march_next<GEO>(F, r, 0x40000000u, steps, st, sx) != 1) break;
     if (cnt < max_k) klist[i * max_k + cnt] = (uint32_t)(r.k - 1);
     ++cnt;
   }
@@ -847,7 +834,7 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
   }
 }
 
-// Rebuild a resident field's bricks and coarse grid from linear bits.
+// Rebuild a resident field's bricks from linear bits.
 __global__ void bricks_from_bits_kernel(FieldDev F, unsigned long long* bricks, const uint32_t* bits) {
   const uint64_t b = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
   const uint64_t nb = (uint64_t)F.Gb * F.Gb * F.Gb;
@@ -864,45 +851,32 @@ __global__ void bricks_from_bits_kernel(FieldDev F, unsigned long long* bricks, 
   bricks[b] = w;
 }
 
-__global__ void coarse_from_bricks_kernel(FieldDev F, uint32_t* coarse) {
-  const uint32_t word = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t nc = F.Gc * F.Gc * F.Gc;
-  if (word >= (nc + 31) / 32) return;
-  const uint32_t per = 1u << (F.cshift - 2);   // bricks per coarse block and axis
-  uint32_t out = 0u;
-  for (uint32_t j = 0; j < 32; ++j) {
-    const uint32_t c = word * 32 + j;
-    if (c >= nc) break;
-    const uint32_t cx = c % F.Gc, cy = (c / F.Gc) % F.Gc, cz = c / (F.Gc * F.Gc);
-    bool any = false;
-    for (uint32_t k = 0; k < per * per * per && !any; ++k) {
-      const uint32_t bx = cx * per + k % per, by = cy * per + (k / per) % per, bz = cz * per + k / (per * per);
-      if (bx < F.Gb && by < F.Gb && bz < F.Gb) any = F.bricks[bx + F.Gb * (by + F.Gb * bz)] != 0ull;
-    }
-    if (any) out |= 1u << j;
+// Chebyshev distance in bricks to the nearest non-empty one (at most 255),
+// one axis a launch: d'(i) = min over j of max(|j - i|, d(i + j)), searched
+// outwards and stopped at the best so far, which a step further out cannot
+// beat.  The first pass reads the bricks themselves.  (Directional distances,
+// one per octant, would save another 5 % of the march's tests for eight times
+// the memory.)
+template <int AXIS>
+__global__ void brick_distance_kernel(FieldDev F, const uint8_t* in, uint8_t* out) {
+  const uint32_t Gb = F.Gb, i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= Gb * Gb * Gb) return;
+  constexpr int kNone = 255;
+  auto at = [&](uint32_t b) -> int {
+    if constexpr (AXIS == 0) return F.bricks[b] != 0ull ? 0 : kNone;
+    else return in[b];
+  };
+  const int c = (int)(AXIS == 0 ? i % Gb : AXIS == 1 ? (i / Gb) % Gb : i / (Gb * Gb));
+  const uint32_t pitch = AXIS == 0 ? 1u : AXIS == 1 ? Gb : Gb * Gb;
+  int best = at(i);
+  for (int j = 1; j < best; ++j) {
+    int v = kNone;
+    if (c >= j) v = at(i - (uint32_t)j * pitch);
+    if (c + j < (int)Gb) v = min(v, at(i + (uint32_t)j * pitch));
+    best = min(best, max(j, v));
+    if (c < j && c + j >= (int)Gb) break;
   }
-  coarse[word] = out;
-}
-
-__global__ void dilate_coarse_kernel(FieldDev F, uint32_t* dil) {
-  const uint32_t word = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t Gc = F.Gc, nc = Gc * Gc * Gc;
-  if (word >= (nc + 31) / 32) return;
-  uint32_t out = 0u;
-  for (uint32_t j = 0; j < 32; ++j) {
-    const uint32_t c = word * 32 + j;
-    if (c >= nc) break;
-    const int cx = (int)(c % Gc), cy = (int)((c / Gc) % Gc), cz = (int)(c / (Gc * Gc));
-    bool any = false;
-    for (int k = 0; k < 27 && !any; ++k) {
-      const int x = cx + k % 3 - 1, y = cy + (k / 3) % 3 - 1, z = cz + k / 9 - 1;
-      if (x < 0 || y < 0 || z < 0 || x >= (int)Gc || y >= (int)Gc || z >= (int)Gc) continue;
-      const uint32_t i = (uint32_t)x + Gc * ((uint32_t)y + Gc * (uint32_t)z);
-      any = (F.coarse[i >> 5] >> (i & 31u)) & 1u;
-    }
-    if (any) out |= 1u << j;
-  }
-  dil[word] = out;
+  out[i] = (uint8_t)best;
 }
 
 // ---------------------------------------------------------------------------
@@ -1013,16 +987,21 @@ hipError_t launch_prune(const FieldDev& F, float alpha, uint32_t npts, int compu
   return hipGetLastError();
 }
 
+hipError_t launch_brick_distance(const FieldDev& F, hipStream_t s) {
+  const dim3 gr((F.Gb * F.Gb * F.Gb + 255u) / 256u), bl(256);
+  uint8_t* d = const_cast<uint8_t*>(F.dist);
+  uint8_t* tmp = reinterpret_cast<uint8_t*>(F.brick_list);
+  hipLaunchKernelGGL(brick_distance_kernel<0>, gr, bl, 0, s, F, nullptr, d);
+  hipLaunchKernelGGL(brick_distance_kernel<1>, gr, bl, 0, s, F, d, tmp);
+  hipLaunchKernelGGL(brick_distance_kernel<2>, gr, bl, 0, s, F, tmp, d);
+  return hipGetLastError();
+}
+
 hipError_t launch_set_occupancy(const FieldDev& F, const uint32_t* bits, hipStream_t s) {
   const uint64_t nb = (uint64_t)F.Gb * F.Gb * F.Gb;
   hipLaunchKernelGGL(bricks_from_bits_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, F,
                      const_cast<unsigned long long*>(F.bricks), bits);
-  const uint32_t words = (F.Gc * F.Gc * F.Gc + 31) / 32;
-  hipLaunchKernelGGL(coarse_from_bricks_kernel, dim3((words + 255) / 256), dim3(256), 0, s, F,
-                     const_cast<uint32_t*>(F.coarse));
-  hipLaunchKernelGGL(dilate_coarse_kernel, dim3((words + 255) / 256), dim3(256), 0, s, F,
-                     const_cast<uint32_t*>(F.coarse_dil));
-  return hipGetLastError();
+  return launch_brick_distance(F, s);
 }
 
 hipError_t phase_cycles(unsigned long long out[kPhaseSlots], bool reset) {
