@@ -341,12 +341,21 @@ vrn_status do_render(vrn_ctx* ctx, Field* f, const vrn_camera* d_cams, uint32_t 
   a.exposure = opts ? std::exp2(opts->exposure_ev) : 1.0f;
   a.budget = (opts && opts->march_budget) ? opts->march_budget : 256u;
   const int compute = opts ? (int)opts->compute : 0;
-  const uint64_t rays = (uint64_t)n_cams * W * H;
-  const uint64_t bt = (uint64_t)render_block_threads(compute);
-  const uint64_t want = (rays + bt - 1) / bt;
-  const uint64_t cap = (uint64_t)ctx->n_cu * render_blocks_per_cu(f->dev, compute);
-  const int grid = (int)std::max<uint64_t>(1, std::min(want, cap));
-  hipError_t e = launch_render(a, compute, grid, s);
+  // Rays a wave carries: the fewest of 16 (one MLP tile), 32 and 64 with which
+  // the waves that fit the chip hold all rays at once.  Fewer rays mean fewer
+  // tiles one after the other in a round (64^2 FP32 room 143 -> 58 us, 256^2
+  // 159 -> 80), but a march shares its instructions among fewer lanes: with
+  // waves that take a second helping 64 rays are faster (16 at 512^2: 145 ->
+  // 180-240 us).  A launch of few waves spreads them over the CUs.
+  const uint64_t rays = (uint64_t)n_cams * ((W + kTile - 1) / kTile) * ((H + kTile - 1) / kTile) * (kTile * kTile);
+  const uint64_t block_waves = (uint64_t)render_block_threads(compute) / 64;
+  const uint64_t blocks = (uint64_t)ctx->n_cu * render_blocks_per_cu(f->dev, compute);
+  const uint64_t fit = blocks * block_waves;
+  a.lanes = rays <= 16 * fit ? 16u : rays <= 32 * fit ? 32u : 64u;
+  const uint64_t waves = (rays + a.lanes - 1) / a.lanes;
+  const uint64_t per_block = std::min(block_waves, (waves + ctx->n_cu - 1) / ctx->n_cu);
+  const int grid = (int)std::min((waves + per_block - 1) / per_block, blocks);
+  hipError_t e = launch_render(a, compute, grid, (int)per_block * 64, s);
   if (e != hipSuccess) return hip_fail(e, "render launch");
   if (!noalloc) {
     track(f, s);

@@ -86,10 +86,19 @@ struct FieldDev {
   uint32_t* brick_count;
 };
 
-// Workspace layout (bytes).  Counters are spaced 64 B apart.
-constexpr int kWsQueue = 0;        // kQueues x u32 at stride 16 u32
-constexpr int kWsDone = 512;       // u32 blocks-finished counter
-constexpr int kWsStats = 576;      // 6 x u64: rays, samples, level fetches, march steps, rounds, tiles
+// Workspace layout (bytes).  A render's counters lie on one 64-byte line per
+// ray queue and are zero between renders.
+constexpr int kStats = 6;          // rays, samples, level fetches, march steps, rounds, tiles
+struct WsQueue {
+  uint32_t taken;                  // rays handed out beyond those dealt by position
+  uint32_t done;                   // finished blocks of the queue
+  unsigned long long stats[kStats];
+  uint64_t pad;
+};
+static_assert(sizeof(WsQueue) == 64, "one line per queue");
+constexpr int kWsQueue = 0;        // kQueues x WsQueue
+constexpr int kWsDone = 512;       // u32 count of finished queues
+constexpr int kWsStats = 576;      // kStats x u64, accumulated over renders
 constexpr int kWsCams = 640;       // kMaxCams x vrn_camera
 constexpr int kWsBytes = 4096;
 // The allocation-free entry point keeps a render's counters (queues, done,
@@ -107,6 +116,7 @@ struct RenderArgs {
   int32_t output;            // vrn_output
   float exposure;            // 2^exposure_ev (VRN_OUT_SRGB)
   uint32_t budget;           // march steps per round
+  uint32_t lanes;            // rays a wave carries at once: its first 16, 32 or all 64 lanes
 };
 
 // launchers (kernels.hip)
@@ -136,7 +146,7 @@ hipError_t debug_counters(unsigned long long out[kDbgSlots], bool reset);
 enum PhaseSlot { kPhRefill = 0, kPhMarch, kPhEncode, kPhMlp, kPhReturn, kPhComposite, kPhaseSlots };
 hipError_t phase_cycles(unsigned long long out[kPhaseSlots], bool reset);
 
-hipError_t launch_render(const RenderArgs& a, int compute, int grid, hipStream_t s);
+hipError_t launch_render(const RenderArgs& a, int compute, int grid, int threads, hipStream_t s);
 int render_blocks_per_cu(const FieldDev& F, int compute);
 hipError_t launch_zero(void* p, uint64_t bytes, hipStream_t s);
 // Device address of the allocation-free entry point's scratch array on

@@ -4,8 +4,8 @@
 // single-kernel interleave of ray marching, hash sampling and MLPs, Sec. 5):
 // persistent waves own 64 rays each (one per lane); every round a wave
 //   1. refills lanes whose ray finished from a per-XCD queue of 8x8 pixel
-//      tiles (XCD-aware: block b works the image slice of XCD b % 8 first,
-//      so each XCD's L2 sees one coherent region of the frame);
+//      tiles (XCD-aware: block b works the queue of XCD b % 8 first, whose
+//      tiles come in long runs, so each XCD's L2 sees coherent regions);
 //   2. marches every ray to its next occupied lattice sample (bounded
 //      number of lattice tests per round, empty bricks skipped);
 //   3. compacts the lanes that found a sample into 16-sample tiles and, per
@@ -16,6 +16,11 @@
 //      or when the march leaves the grid, writing RGBA and sample counts.
 // Counters in the workspace return to zero when the last block finishes, so
 // the launch needs no memset and can be replayed from a HIP graph.
+//
+// A launch that does not fill the chip is bound by the latency of a wave's
+// rounds, one 16-sample tile after the other.  Its waves carry 16 or 32 rays
+// instead of 64 (RenderArgs::lanes), one or two tiles a round, and more waves
+// share the rays.
 #include <map>
 #include <mutex>
 #include <type_traits>
@@ -29,6 +34,7 @@ __device__ unsigned long long vrn_debug_counts[kDbgSlots];
 #endif
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
+constexpr uint32_t kHelped = 2;      // other queues a wave takes rays from when its own is empty
 
 #ifdef VRN_PHASE_TIMING
 __device__ unsigned long long vrn_phase_cycles[kPhaseSlots];
@@ -185,7 +191,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   __shared__ LevelDev s_lv[kMaxLevels];
   __shared__ uint32_t s_off[kMaxCams + 1];
   __shared__ uint32_t s_rb[kMaxCams], s_re[kMaxCams];
-  __shared__ uint32_t s_stats[6];
+  __shared__ uint32_t s_stats[kStats];
   // per-ray SH values: FP32 [lane][g] float4 (FP32 path) or packed 16-bit [lane][g] uint2
   __shared__ __align__(16) uint8_t s_sh_raw[kThreads * 4 * (kF32Class<MODE> ? 16 : 8)];
   uint2* s_sh = reinterpret_cast<uint2*>(s_sh_raw);
@@ -196,7 +202,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   const __amdgpu_buffer_rsrc_t tab = table_rsrc(F);
   load_weights<MODE>(F, s_w, s_b);
   if (threadIdx.x < F.L) s_lv[threadIdx.x] = F.levels[threadIdx.x];
-  if (threadIdx.x < 6) s_stats[threadIdx.x] = 0;
+  if (threadIdx.x < kStats) s_stats[threadIdx.x] = 0;
   const uint32_t tx = (A.W + kTile - 1) / kTile;
   const float inv_tx = 1.0f / (float)tx;
   if (threadIdx.x == 0) {
@@ -207,18 +213,31 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
       s_off[c] = acc;
       s_rb[c] = rb;
       s_re[c] = re;
-      acc += tx * ((re - rb + kTile - 1) / kTile) * (kTile * kTile);
+      acc += tx * ((re - rb + kTile - 1) / kTile);
     }
     s_off[A.n_cams] = acc;
   }
   __syncthreads();
 
   const int lane = lane_id();
-  const uint32_t n_tiles = s_off[A.n_cams] / (kTile * kTile);
-  uint32_t* ctrl = reinterpret_cast<uint32_t*>(A.ws + kWsQueue);
-  int q = (int)(blockIdx.x % kQueues);
-  int q_tried = 0;
-  bool out_of_work = false;
+  const uint32_t n_tiles = s_off[A.n_cams];
+  WsQueue* queues = reinterpret_cast<WsQueue*>(A.ws + kWsQueue);
+  // Tiles go to the queues in runs of 2^run, each turn starting one queue
+  // further, so that no queue is left with the same columns of every row.
+  // 64 runs a frame balance the queues, and still leave an XCD's L2 whole tile
+  // rows of a large frame (shorter runs cost the 2x2048^2 house frame 1 %).  A
+  // queue's ids count its own tiles' pixels: the first dealt(q) go to its
+  // blocks' waves by position, the rest as lanes fall free, and what is left
+  // of the next two queues then.  An atomic on a line that other XCDs share
+  // takes some 20 ns, one after another: drawing every ray through them and
+  // trying all eight queues at the end cost each launch 50-90 us (an empty
+  // 512^2 frame 114 us, now 27).
+  const uint32_t nq = gridDim.x >= (uint32_t)kQueues ? (uint32_t)kQueues : 1u, wpb = blockDim.x >> 6;
+  const uint32_t run = n_tiles < 128u ? 0u : 25u - (uint32_t)__clz((int)n_tiles);
+  const uint32_t size = ((((n_tiles + (1u << run) - 1u) >> run) + nq - 1u) / nq << run) * (kTile * kTile);
+  auto dealt = [&](uint32_t i) { return (gridDim.x + nq - 1u - i) / nq * wpb * A.lanes; };
+  uint32_t q = blockIdx.x % nq, tried = 0;
+  bool dealing = true, out_of_work = false;
 
   Ray r;
   r.k = 0;
@@ -232,7 +251,8 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   r.ox = r.oy = r.oz = r.dx = r.dy = r.dz = 0.0f;
   uint32_t pix = kNone, n = 0;
   float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
-  uint32_t st_steps = 0, st_fetch = 0, st_samples = 0, st_rays = 0, st_rounds = 0, st_tiles = 0;
+  uint32_t st_steps = 0, st_fetch = 0;                               // per lane
+  uint32_t st_samples = 0, st_rays = 0, st_rounds = 0, st_tiles = 0;  // of the wave
 
   VRN_PHASE_START();
   auto retire = [&]() {
@@ -250,7 +270,6 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     VRN_DEBUG_COUNT((uint64_t)pix >= (uint64_t)A.n_cams * A.H * A.W, kDbgPixel);
     reinterpret_cast<float4*>(A.rgba)[pix] = v;
     if (A.nsamples) A.nsamples[pix] = n;
-    ++st_rays;
     pix = kNone;
   };
 
@@ -261,29 +280,41 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     VRN_PHASE(kPhComposite);
     // ---- 1. refill lanes that have no ray -------------------------------
     while (!out_of_work) {
-      const uint64_t need = __ballot(pix == kNone);
+      const bool open = pix == kNone && (uint32_t)lane < A.lanes;
+      const uint64_t need = __ballot(open);
       if (need == 0) break;
-      const int cnt = __popcll(need);
-      const int leader = __ffsll((unsigned long long)need) - 1;
-      uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(&ctrl[q * 16], (uint32_t)cnt);
-      base = (uint32_t)shfl_i((int)base, leader);
-      const uint32_t qb = (uint32_t)((uint64_t)n_tiles * q / kQueues) * (kTile * kTile);
-      const uint32_t qe = (uint32_t)((uint64_t)n_tiles * (q + 1) / kQueues) * (kTile * kTile);
-      if (pix == kNone) {
-        const int rank = __popcll(need & ((1ull << lane) - 1ull));
-        const uint32_t id = qb + base + (uint32_t)rank;
-        if (id < qe) {
+      uint32_t base;
+      if (dealing) {
+        base = (blockIdx.x / nq * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * A.lanes;
+        dealing = false;
+      } else {
+        base = dealt(q);
+        uint32_t taken = 0;
+        if (base < size) {
+          if (lane == 0) taken = atomicAdd(&queues[q].taken, (uint32_t)__popcll(need));
+          base += (uint32_t)__builtin_amdgcn_readfirstlane((int)taken);
+        }
+        if (base >= size) {
+          if (++tried > kHelped) out_of_work = true;
+          q = q + 1u == nq ? 0u : q + 1u;
+          continue;
+        }
+      }
+      if (open) {
+        const uint32_t id = base + (uint32_t)__popcll(need & ((1ull << lane) - 1ull));
+        const uint32_t own = id / (kTile * kTile), within = id % (kTile * kTile);
+        const uint32_t turn = own >> run;
+        const uint32_t tile = ((turn * nq + ((q + turn) & (nq - 1u))) << run) + (own & ((1u << run) - 1u));
+        if (tile < n_tiles) {
           uint32_t c = 0;
-          while (c + 1 < A.n_cams && id >= s_off[c + 1]) ++c;
-          const uint32_t local = id - s_off[c];
-          const uint32_t tile = local / (kTile * kTile), within = local % (kTile * kTile);
-          // tile / tx without an integer division: float quotient, then an
-          // exact integer correction (tile < 2^24)
-          uint32_t ty = (uint32_t)((float)tile * inv_tx);
-          if (ty * tx > tile) --ty;
-          else if ((ty + 1) * tx <= tile) ++ty;
-          const uint32_t col = (tile - ty * tx) * kTile + within % kTile;
+          while (c + 1 < A.n_cams && tile >= s_off[c + 1]) ++c;
+          const uint32_t local = tile - s_off[c];
+          // local / tx without an integer division: float quotient, then an
+          // exact integer correction (local < 2^24)
+          uint32_t ty = (uint32_t)((float)local * inv_tx);
+          if (ty * tx > local) --ty;
+          else if ((ty + 1) * tx <= local) ++ty;
+          const uint32_t col = (local - ty * tx) * kTile + within % kTile;
           const uint32_t row = s_rb[c] + ty * kTile + within / kTile;
           if (col < A.W && row < s_re[c]) {
             setup_ray<GEO>(F, A.cams[c], col, row, r);
@@ -296,10 +327,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
           }
         }
       }
-      if (qb + base + (uint32_t)cnt >= qe) {
-        q = (q + 1) % kQueues;
-        if (++q_tried >= kQueues) out_of_work = true;
-      }
+      st_rays += (uint32_t)__popcll(__ballot(open && pix != kNone));
     }
     VRN_PHASE(kPhRefill);
     if (__ballot(pix != kNone) == 0) break;
@@ -324,10 +352,9 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     const int wave_base = (threadIdx.x >> 6) << 6;
     if (has) s_slot[wave_base + rank] = (uint32_t)lane;
     __builtin_amdgcn_wave_barrier();
-    if (lane == 0) {
-      ++st_rounds;
-      st_tiles += (uint32_t)nt;
-    }
+    ++st_rounds;
+    st_tiles += (uint32_t)nt;
+    st_samples += (uint32_t)ns;
 
     VRN_PHASE(kPhMarch);
     // ---- 3. encode + MLP of the compacted samples -------------------------
@@ -426,30 +453,47 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
       cb = fmaf(wgt, sigmoidf<kFast>(sl2), cb);
       T = T * trans;
       ++n;
-      ++st_samples;
       if (T < F.t_min || n >= F.max_samples) retire();
     }
   }
 
   VRN_PHASE(kPhRefill);
   VRN_PHASE_FLUSH();
-  atomicAdd(&s_stats[0], st_rays);
-  atomicAdd(&s_stats[1], st_samples);
   atomicAdd(&s_stats[2], st_fetch);
   atomicAdd(&s_stats[3], st_steps);
-  atomicAdd(&s_stats[4], st_rounds);
-  atomicAdd(&s_stats[5], st_tiles);
+  if (lane == 0) {
+    atomicAdd(&s_stats[0], st_rays);
+    atomicAdd(&s_stats[1], st_samples);
+    atomicAdd(&s_stats[4], st_rounds);
+    atomicAdd(&s_stats[5], st_tiles);
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long* stats = reinterpret_cast<unsigned long long*>(A.ws + kWsStats);
-    for (int i = 0; i < 6; ++i) atomicAdd(&stats[i], (unsigned long long)s_stats[i]);
+  // Statistics and the count of finished blocks gather on the line of the
+  // block's own queue, six lanes at once; its last block counts the queue as
+  // finished, and the last of those adds the queues' sums up and leaves every
+  // counter at zero.
+  if (threadIdx.x < 64) {
+    WsQueue& own = queues[blockIdx.x % nq];
+    if (lane < kStats) atomicAdd(&own.stats[lane], (unsigned long long)s_stats[lane]);
     __threadfence();
-    uint32_t* done = reinterpret_cast<uint32_t*>(A.ws + kWsDone);
-    if (atomicAdd(done, 1u) == gridDim.x - 1) {
-      for (int i = 0; i < kQueues; ++i) atomicExch(&ctrl[i * 16], 0u);
-      atomicExch(done, 0u);
+    bool last = false;
+    if (lane == 0 && atomicAdd(&own.done, 1u) == (gridDim.x + nq - 1u - blockIdx.x % nq) / nq - 1u) {
       __threadfence();
+      last = atomicAdd(reinterpret_cast<uint32_t*>(A.ws + kWsDone), 1u) == nq - 1u;
     }
+    if (__ballot(last) == 0) return;
+    __threadfence();
+    if (lane < kStats) {
+      unsigned long long sum = 0;
+      for (int i = 0; i < kQueues; ++i) sum += atomicExch(&queues[i].stats[lane], 0ull);
+      atomicAdd(reinterpret_cast<unsigned long long*>(A.ws + kWsStats) + lane, sum);
+    }
+    if (lane < kQueues) {
+      atomicExch(&queues[lane].taken, 0u);
+      atomicExch(&queues[lane].done, 0u);
+    }
+    if (lane == 0) atomicExch(reinterpret_cast<uint32_t*>(A.ws + kWsDone), 0u);
+    __threadfence();
   }
 }
 
@@ -931,8 +975,8 @@ static void launch_render_geo(const RenderArgs& a, int compute, dim3 gr, dim3 bl
   }
 }
 
-hipError_t launch_render(const RenderArgs& a, int compute, int grid, hipStream_t s) {
-  const dim3 gr(grid), bl(render_block_threads(compute));
+hipError_t launch_render(const RenderArgs& a, int compute, int grid, int threads, hipStream_t s) {
+  const dim3 gr(grid), bl(threads);
   if (a.F.lat) launch_render_geo<1>(a, compute, gr, bl, s);
   else launch_render_geo<0>(a, compute, gr, bl, s);
   return hipGetLastError();
