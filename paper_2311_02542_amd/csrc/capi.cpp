@@ -504,10 +504,11 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
       lat[k + 1] = t;
     }
   }
+  const uint64_t n_groups = (uint64_t)((Gb + 3) / 4) * Gb * Gb;   // of four bricks along x (pruning)
   const uint64_t tab_bytes = n_tab * (d->table_dtype == VRN_F16 ? 2 : 4);
   const uint64_t need = tab_bytes + bricks.size() * 8 + (w32.size() + bias.size()) * 4 +
                         (w16.size() + wbf.size() + wx3.size()) * 2 + lv.size() * sizeof(LevelDev) + lat.size() * 4 +
-                        bricks.size() * 5 + 256;
+                        bricks.size() + n_groups * sizeof(uint2) + 256;
   if (ctx->budget && ctx->used + need > ctx->budget)
     return fail(VRN_ERR_BUDGET, "loading the field would exceed the HBM budget");
 
@@ -519,7 +520,8 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
   LevelDev* dlv = nullptr;
   unsigned long long* dbr = nullptr;
   float *dw32 = nullptr, *dbias = nullptr, *dlat = nullptr;
-  uint32_t *dlist = nullptr, *dcount = nullptr;
+  uint2* dlist = nullptr;
+  uint32_t* dcount = nullptr;
   uint8_t* ddist = nullptr;
   const std::vector<uint32_t> zeros(64, 0u);
   uint16_t *dw16 = nullptr, *dwbf = nullptr, *dwx3 = nullptr;
@@ -530,7 +532,7 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
       (e = upload(f, wx3.data(), wx3.size(), &dwx3)) ||
       (e = upload(f, bias.data(), bias.size(), &dbias)) ||
       (use_table && (e = upload(f, lat.data(), lat.size(), &dlat))) ||
-      (e = alloc_only(f, bricks.size(), &ddist)) || (e = alloc_only(f, bricks.size(), &dlist)) || (e = upload(f, zeros.data(), zeros.size(), &dcount)) ||
+      (e = alloc_only(f, bricks.size(), &ddist)) || (e = alloc_only(f, (size_t)n_groups, &dlist)) || (e = upload(f, zeros.data(), zeros.size(), &dcount)) ||
       (e = hipEventCreateWithFlags(&f->noalloc_ev, hipEventDisableTiming))) {
     free_field(f);
     return e == hipErrorOutOfMemory ? fail(VRN_ERR_OUT_OF_MEMORY, "device allocation failed")
@@ -540,8 +542,8 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
   F.levels = dlv;
   F.bricks = dbr;
   F.dist = ddist;
-  F.brick_list = dlist;
-  F.brick_count = dcount;
+  F.group_list = dlist;
+  F.group_total = reinterpret_cast<unsigned long long*>(dcount);
   F.w32 = dw32;
   F.w16 = dw16;
   F.wbf = dwbf;

@@ -20,6 +20,8 @@ constexpr int kBlock = 256;         // threads per render block (4 waves)
 constexpr int kBlockF32 = 1024;
 inline int render_block_threads(int compute) { return (compute == 0 || compute == 3) ? kBlockF32 : kBlock; }
 constexpr int kHidden = 64;
+constexpr int kMaxDist = 16;        // longest brick distance held: one of 8 already takes the house scene's
+                                    // march as far per ray to within 0.2 %
 constexpr int kMlpBatch = 1;        // 16-sample tiles per 16-bit MLP call (weights read once per call)
 
 // MFMA fragment layout of the MLP weights (see mlp_tile in device.hpp).
@@ -49,7 +51,7 @@ struct FieldDev {
   const LevelDev* levels;    // [L]
   const unsigned long long* bricks;  // Gb^3 bricks of 4x4x4 cells, bit (x&3) + 4 (y&3) + 16 (z&3)
   const uint8_t* dist;       // [Gb^3] bricks to the nearest non-empty one (Chebyshev; 0: non-empty;
-                             // at most 255, which also stands for none)
+                             // at most kMaxDist, which also stands for none)
   const float* w32;          // kW32Total
   const uint16_t* w16;       // kW16Total fp16 bits
   const uint16_t* wbf;       // kW16Total bf16 bits
@@ -79,11 +81,11 @@ struct FieldDev {
   float lod_c2;              // ln(2 s): LOD constant when the footprint is already normalised
   uint32_t d1_ksteps;        // FP32 k-steps of the first density layer
   uint32_t c1_ksteps;        // FP32 k-steps of the first color layer
-  // grid pruning: the non-empty bricks, listed on the device by each
-  // vrn_prune_grid call ([Gb^3] entries, count in its own 256-byte block);
-  // between its uses scratch of the distance build
-  uint32_t* brick_list;
-  uint32_t* brick_count;
+  // grid pruning: the non-empty groups of four bricks along x, listed on the
+  // device by each vrn_prune_grid call ([ceil(Gb / 4) Gb^2] entries; totals in
+  // their own 256-byte block); between its uses scratch of the distance build
+  uint2* group_list;
+  unsigned long long* group_total;
 };
 
 // Workspace layout (bytes).  A render's counters lie on one 64-byte line per
@@ -162,7 +164,7 @@ hipError_t launch_encode(const FieldDev& F, const float* xyz, const float* t, co
 hipError_t launch_prune(const FieldDev& F, float alpha, uint32_t npts, int compute, uint32_t* bits_out,
                         float* max_op, int n_cu, hipStream_t s);
 hipError_t launch_set_occupancy(const FieldDev& F, const uint32_t* bits, hipStream_t s);
-// The distance grid of the field's bricks (F.dist), with F.brick_list as scratch.
+// The distance grid of the field's bricks (F.dist), with F.group_list as scratch.
 hipError_t launch_brick_distance(const FieldDev& F, hipStream_t s);
 hipError_t launch_mlp(const FieldDev& F, const float* feat, const float* dir, uint32_t n,
                       int compute, float* sigma, float* rgb, hipStream_t s);

@@ -602,13 +602,28 @@ __global__ __launch_bounds__(kBlock) void mlp_kernel(FieldDev F, const float* fe
 // occupied voxel, threshold alpha; pruning only clears bits.
 //
 // Three launches: (1) the output bits start as the field's occupancy (and
-// the maximum opacity of every unoccupied voxel as NaN); (2) the non-empty
-// 4x4x4 bricks are listed; (3) persistent waves walk that list (wave w takes
-// entries w, w + n_waves, ...), queue each brick's occupied voxels in LDS,
-// and evaluate them 64 voxels at a time -- 16-sample MFMA tiles of the
-// voxels' points through the same encode and density layers as the
-// renderer -- then clear the bits of voxels below alpha.  Only occupied
-// voxels cost work, and the weights are staged once per resident block.
+// the maximum opacity, by a launch of its own, as NaN); (2) the non-empty
+// groups of four bricks along x are listed with their places in the order of
+// all occupied voxels; (3) persistent waves take chunks of that order, look
+// the chunk's first group up, gather its voxels row by row in LDS and
+// evaluate them -- 16-sample MFMA tiles through the same encode and density
+// layers as the renderer -- then clear the bits of voxels below alpha.  Only
+// occupied voxels cost work, and the weights are staged once per resident
+// block.
+//
+// What bounds it is the fabric behind the L2s: on the 512^3 house field (4.0 M
+// voxels x 4 points x 16 levels) the finer levels' corners miss L2, a
+// 128-byte line each, at 7.5 TB/s; the FP32 and FP16 MLPs take the same time.
+// The hash keeps the 32 cells of an aligned run along x in one line, so what
+// shares lines is neighbours along x and, on the coarser levels, all
+// neighbours, if they are looked up at about the same time: the L2 has room
+// for some 40 lines a wave.  A tile is therefore the same point of up to 16
+// voxels along x, and the waves of an XCD take neighbouring chunks of 16 side
+// by side.  FP16, 4 points: 6.40 ms with whole bricks dealt to the waves of all
+// XCDs in turn and four points of four voxels a tile, 6.05 ms with one
+// contiguous share a wave, 5.72, 5.60 and 5.40 ms with chunks of 64, 32 and 16
+// voxels (8 points: 9.36 -> 6.49 ms).  Other cache policies of the gathers cost
+// 4 % (device scope) to 50 % (non-temporal).
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ bool cell_occupied(const FieldDev& F, uint32_t x, uint32_t y, uint32_t z) {
@@ -630,14 +645,14 @@ __device__ __forceinline__ float voxel_offset(uint32_t npts, uint32_t p, uint32_
 }
 
 // (1) one thread per 32-bit output word (G^3 < 2^31, so 32-bit indices)
-__global__ void prune_init_kernel(FieldDev F, uint32_t* bits_out, float* max_op) {
+__global__ void prune_init_kernel(FieldDev F, uint32_t* bits_out) {
   const uint32_t G = F.G;
   const uint32_t n = G * G * G;
   const uint32_t w = blockIdx.x * blockDim.x + threadIdx.x;
   if (w >= (n + 31u) / 32u) return;
   const uint32_t i0 = w * 32u;
   uint32_t x = i0 % G, y = (i0 / G) % G, z = i0 / (G * G);
-  if ((G & 31u) == 0u && !max_op) {
+  if ((G & 31u) == 0u) {
     // the word is one row of 32 cells at fixed (y, z): 4 cells from each of
     // 8 bricks, taken from the brick words directly
     const uint32_t shift = 4u * (y & 3u) + 16u * (z & 3u);
@@ -651,7 +666,6 @@ __global__ void prune_init_kernel(FieldDev F, uint32_t* bits_out, float* max_op)
   uint32_t out = 0u;
   for (uint32_t j = 0; j < 32u && i0 + j < n; ++j) {
     if (cell_occupied(F, x, y, z)) out |= 1u << j;
-    else if (max_op) max_op[i0 + j] = __builtin_nanf("");
     if (++x == G) {
       x = 0;
       if (++y == G) {
@@ -663,19 +677,40 @@ __global__ void prune_init_kernel(FieldDev F, uint32_t* bits_out, float* max_op)
   bits_out[w] = out;
 }
 
-// (2) indices of the non-empty bricks, in any order (count zeroed before)
-__global__ void brick_list_kernel(FieldDev F, uint32_t* list, uint32_t* count) {
-  const uint32_t nb = F.Gb * F.Gb * F.Gb;
-  const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-  const bool nz = b < nb && F.bricks[b] != 0ull;
-  const uint64_t m = __ballot(nz);
+// the maximum opacity of every voxel starts as NaN; the occupied ones are
+// written by the pass (at 512^3 a write stream of 0.5 GB; together with the
+// bits, a thread a word, it took 1.6 ms)
+__global__ void nan_kernel(float* p, uint64_t n) {
+  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+    p[i] = __builtin_nanf("");
+}
+
+// (2) the non-empty groups of four bricks along x, nearly in order: x the
+// index gx + ngx (by + Gb bz) with ngx = ceil(Gb / 4), y the number of
+// occupied voxels of the groups listed before.  total (zeroed before): groups
+// in the high word, voxels in the low one.
+__global__ void group_list_kernel(FieldDev F, uint2* list, unsigned long long* total) {
+  const uint32_t ngx = (F.Gb + 3u) / 4u, n = ngx * F.Gb * F.Gb;
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  uint32_t voxels = 0;
+  if (i < n) {
+    const uint32_t gx = i % ngx, row = i / ngx, b = row * F.Gb + 4u * gx;
+    for (uint32_t j = 0; j < 4u && 4u * gx + j < F.Gb; ++j) voxels += (uint32_t)__popcll(F.bricks[b + j]);
+  }
+  const uint64_t m = __ballot(voxels != 0u);
   if (m == 0) return;
   const int lane = lane_id();
-  const int leader = __ffsll((unsigned long long)m) - 1;
-  uint32_t base = 0;
-  if (lane == leader) base = atomicAdd(count, (uint32_t)__popcll(m));
-  base = (uint32_t)shfl_i((int)base, leader);
-  if (nz) list[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = b;
+  uint32_t upto = voxels;
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) {
+    const uint32_t o = (uint32_t)shfl_i((int)upto, lane - d);
+    if (lane >= d) upto += o;
+  }
+  unsigned long long base = 0;
+  if (lane == 63) base = atomicAdd(total, (unsigned long long)__popcll(m) << 32 | upto);
+  const uint32_t entry = (uint32_t)__builtin_amdgcn_readlane((int)(base >> 32), 63);
+  const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)base, 63);
+  if (voxels != 0u) list[entry + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = make_uint2(i, before + upto - voxels);
 }
 
 // Density layers only (the pruning pass needs sigma, not color), in the
@@ -764,18 +799,17 @@ struct DensitySmem {
   static constexpr int kBytes = (MODE == 0) ? kW32_C1 * 4 : (MODE == 3 ? 3 * kW16_C1 * 2 : kW16_C1 * 2);
 };
 
-constexpr int kPruneQueue = 128;   // per-wave voxel queue: < 64 carried + one brick
+constexpr uint32_t kPruneChunk = 16;   // voxels a wave takes at once
 
-// (3) persistent pruning waves over the brick list.  TET: 4 points per voxel.
-template <bool TAB16, int MODE, bool TET>
+// (3) persistent pruning waves over the group list.
+template <bool TAB16, int MODE>
 __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, uint32_t npts, uint32_t p,
-                                                      const uint32_t* list, const uint32_t* count,
+                                                      const uint2* list, const unsigned long long* total,
                                                       uint32_t* bits_out, float* max_op) {
   __shared__ __align__(16) uint8_t s_w[DensitySmem<MODE>::kBytes];
   __shared__ float s_b[kBiasTotal];
   __shared__ LevelDev s_lv[kMaxLevels];
-  __shared__ uint32_t s_q[kBlock / 64][kPruneQueue];
-  __shared__ uint32_t s_max[kBlock / 64][64];
+  __shared__ uint32_t s_q[kBlock / 64][kPruneChunk];
   {
     const uint4* src = weight_src<MODE>(F);
     uint4* dst = reinterpret_cast<uint4*>(s_w);
@@ -793,51 +827,60 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
   const __amdgpu_buffer_rsrc_t tab = table_rsrc(F);
   const int lane = lane_id(), g = lane >> 4, wv = threadIdx.x >> 6;
   uint32_t* q = s_q[wv];
-  uint32_t* mx = s_max[wv];
-  const uint32_t n_list = *count;
-  const uint32_t n_waves = gridDim.x * (kBlock / 64);
-  const uint32_t G = F.G, Gb = F.Gb;
+  // Each XCD takes an eighth of the voxels, in list order, and its waves one
+  // chunk of it after the other side by side, so that neighbours meet in one L2.
+  const uint32_t nx = gridDim.x >= (uint32_t)kQueues ? (uint32_t)kQueues : 1u, xcd = blockIdx.x % nx;
+  const uint32_t n_list = (uint32_t)(*total >> 32), n_vox = (uint32_t)*total;
+  const uint32_t stop = (uint32_t)((uint64_t)n_vox * (xcd + 1u) / nx);
+  const uint32_t stride = (gridDim.x + nx - 1u - xcd) / nx * (kBlock / 64) * kPruneChunk;
+  // p points along x of a voxel (p^3 patterns) stand side by side in a tile
+  const uint32_t sx = npts == 4u ? 1u : p, vpt = 16u / sx;
+  const uint32_t vl = ((uint32_t)lane & 15u) / sx, px = ((uint32_t)lane & 15u) - vl * sx;
+  const uint32_t G = F.G, Gb = F.Gb, ngx = (Gb + 3u) / 4u;
   const float cell = F.inv_cs;
-  int qn = 0;
-  for (uint32_t i = blockIdx.x * (kBlock / 64) + (uint32_t)wv;; i += n_waves) {
-    const bool more = i < n_list;
-    if (more) {
-      // queue the occupied voxels of one brick, packed x | y << 10 | z << 20
-      const uint32_t b = list[i];
-      const unsigned long long w = F.bricks[b];
-      const uint32_t bx = b % Gb, by = (b / Gb) % Gb, bz = b / (Gb * Gb);
-      if ((w >> lane) & 1ull) {
-        const int rank = __popcll(w & ((1ull << lane) - 1ull));
-        const uint32_t x = 4u * bx + ((uint32_t)lane & 3u), y = 4u * by + (((uint32_t)lane >> 2) & 3u),
-                       z = 4u * bz + ((uint32_t)lane >> 4);
-        q[qn + rank] = x | (y << 10) | (z << 20);
+  for (uint32_t begin = (uint32_t)((uint64_t)n_vox * xcd / nx) +
+                        (blockIdx.x / nx * (kBlock / 64) + (uint32_t)wv) * kPruneChunk;
+       begin < stop; begin += stride) {
+    const uint32_t end = min(begin + kPruneChunk, stop);
+    uint32_t i = 0;                     // the last entry that starts at or before begin
+    for (uint32_t hi = n_list; hi - i > 1u;) {
+      const uint32_t mid = i + (hi - i) / 2u;
+      if (list[mid].y <= begin) i = mid;
+      else hi = mid;
+    }
+    for (; i < n_list; ++i) {
+      const uint2 entry = list[i];
+      if (entry.y >= end) break;
+      // queue the occupied voxels of one group, rows of 16 along x one after
+      // another, packed x | y << 10 | z << 20; lane 4 r + j holds row r of
+      // brick j
+      const uint32_t e = entry.x, j = (uint32_t)lane & 3u, r = (uint32_t)lane >> 2;
+      const uint32_t bx = 4u * (e % ngx) + j, by = (e / ngx) % Gb, bz = e / (ngx * Gb);
+      const uint32_t four = bx < Gb ? (uint32_t)(F.bricks[bx + Gb * (by + Gb * bz)] >> (4u * r)) & 15u : 0u;
+      uint32_t at = entry.y;            // place of the lane's first voxel in list order
+#pragma unroll
+      for (uint32_t k = 0; k < 4u; ++k) {
+        const uint64_t m = __ballot((four >> k) & 1u);
+        at += (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
       }
-      qn += __popcll(w);
+      const uint32_t v = (4u * bx) | ((4u * by + (r & 3u)) << 10) | ((4u * bz + (r >> 2)) << 20);
+#pragma unroll
+      for (uint32_t k = 0; k < 4u; ++k)
+        if ((four >> k) & 1u) {
+          if (at >= begin && at < end) q[at - begin] = v + k;
+          ++at;
+        }
     }
     __builtin_amdgcn_wave_barrier();
-    while (qn >= 64 || (!more && qn > 0)) {
-      asm volatile("" ::: "memory");
-      const int V = qn < 64 ? qn : 64;
-      mx[lane] = 0u;
-      __builtin_amdgcn_wave_barrier();
-      const int ns = V * (int)npts;
-      for (int t = 0; t * 16 < ns; ++t) {
+    const int V = (int)(end - begin);
+    for (int t = 0; t < V; t += (int)vpt) {
+      const int vr = t + (int)vl;
+      const bool act = vl < vpt && vr < V;
+      const uint32_t c = q[act ? vr : 0];
+      const uint32_t cc[3] = {c & 1023u, (c >> 10) & 1023u, c >> 20};
+      float most = 0.0f;
+      for (uint32_t pi = px; pi < npts; pi += sx) {
         asm volatile("" ::: "memory");
-        const int s = t * 16 + (lane & 15);
-        const bool act = s < ns;
-        int vr = 0;
-        uint32_t pi = 0;
-        if (act) {
-          if constexpr (TET) {
-            vr = s >> 2;
-            pi = (uint32_t)s & 3u;
-          } else {
-            vr = s / (int)npts;
-            pi = (uint32_t)(s - vr * (int)npts);
-          }
-        }
-        const uint32_t c = q[vr];
-        const uint32_t cc[3] = {c & 1023u, (c >> 10) & 1023u, c >> 20};
         float x[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) x[a] = F.amin[a] + ((float)cc[a] + voxel_offset(npts, p, pi, a)) * cell;
@@ -852,39 +895,42 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
           o0 = density_tile_x3(reinterpret_cast<const uint4*>(s_w), s_b, feat, lane);
         else
           o0 = density_tile_16<MODE == 2>(reinterpret_cast<const uint4*>(s_w), s_b, feat, lane);
-        if (act && g == 0) {
-          float op = 1.0f - expf(-expf(o0) * F.dt);
-          // a NaN opacity (16-bit activations that overflowed) keeps the voxel
-          if (!(op == op)) op = 1.0f;
-          atomicMax(&mx[vr], __float_as_uint(fmaxf(op, 0.0f)));
-        }
+        float op = 1.0f - expf(-expf(o0) * F.dt);
+        // a NaN opacity (16-bit activations that overflowed) keeps the voxel
+        if (!(op == op)) op = 1.0f;
+        most = fmaxf(most, op);
       }
-      __builtin_amdgcn_wave_barrier();
-      if (lane < V) {
-        const uint32_t c = q[lane];
-        const uint32_t idx = (c & 1023u) + G * (((c >> 10) & 1023u) + G * (c >> 20));
-        const float m = __uint_as_float(mx[lane]);
-        if (!(m >= alpha)) atomicAnd(&bits_out[idx >> 5], ~(1u << (idx & 31u)));
-        if (max_op) max_op[idx] = m;
+      float top = most;
+      for (uint32_t k = 1; k < sx; ++k) top = fmaxf(top, shfl_f(most, lane + (int)k));
+      if (act && g == 0 && px == 0u) {
+        const uint32_t idx = cc[0] + G * (cc[1] + G * cc[2]);
+        if (!(top >= alpha)) atomicAnd(&bits_out[idx >> 5], ~(1u << (idx & 31u)));
+        if (max_op) max_op[idx] = top;
       }
-      // drop the V evaluated voxels from the front of the queue
-      const uint32_t tail = lane + V < qn ? q[lane + V] : 0u;
-      __builtin_amdgcn_wave_barrier();
-      if (lane + V < qn) q[lane] = tail;
-      __builtin_amdgcn_wave_barrier();
-      qn -= V;
     }
-    if (!more) break;
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
-// Rebuild a resident field's bricks from linear bits.
+// Rebuild a resident field's bricks from linear bits.  With the distances
+// below 97 us at 512^3, where bricks by single cells and a coarse grid and its
+// dilation by a few serial threads took 700 us.
 __global__ void bricks_from_bits_kernel(FieldDev F, unsigned long long* bricks, const uint32_t* bits) {
   const uint64_t b = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
   const uint64_t nb = (uint64_t)F.Gb * F.Gb * F.Gb;
   if (b >= nb) return;
   const uint32_t bx = (uint32_t)(b % F.Gb), by = (uint32_t)((b / F.Gb) % F.Gb), bz = (uint32_t)(b / ((uint64_t)F.Gb * F.Gb));
   unsigned long long w = 0ull;
+  if ((F.G & 3u) == 0u) {
+    // four cells of a row lie in one word: 16 loads, not 64
+#pragma unroll
+    for (uint32_t r = 0; r < 16; ++r) {
+      const uint64_t idx = 4 * bx + (uint64_t)F.G * (4 * by + (r & 3) + (uint64_t)F.G * (4 * bz + (r >> 2)));
+      w |= (unsigned long long)((bits[idx >> 5] >> (idx & 31)) & 15u) << (4 * r);
+    }
+    bricks[b] = w;
+    return;
+  }
   for (uint32_t i = 0; i < 64; ++i) {
     const uint32_t x = 4 * bx + (i & 3), y = 4 * by + ((i >> 2) & 3), z = 4 * bz + (i >> 4);
     if (x < F.G && y < F.G && z < F.G) {
@@ -895,7 +941,7 @@ __global__ void bricks_from_bits_kernel(FieldDev F, unsigned long long* bricks, 
   bricks[b] = w;
 }
 
-// Chebyshev distance in bricks to the nearest non-empty one (at most 255),
+// Chebyshev distance in bricks to the nearest non-empty one (at most kMaxDist),
 // one axis a launch: d'(i) = min over j of max(|j - i|, d(i + j)), searched
 // outwards and stopped at the best so far, which a step further out cannot
 // beat.  The first pass reads the bricks themselves.  (Directional distances,
@@ -905,16 +951,15 @@ template <int AXIS>
 __global__ void brick_distance_kernel(FieldDev F, const uint8_t* in, uint8_t* out) {
   const uint32_t Gb = F.Gb, i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= Gb * Gb * Gb) return;
-  constexpr int kNone = 255;
   auto at = [&](uint32_t b) -> int {
-    if constexpr (AXIS == 0) return F.bricks[b] != 0ull ? 0 : kNone;
+    if constexpr (AXIS == 0) return F.bricks[b] != 0ull ? 0 : kMaxDist;
     else return in[b];
   };
   const int c = (int)(AXIS == 0 ? i % Gb : AXIS == 1 ? (i / Gb) % Gb : i / (Gb * Gb));
   const uint32_t pitch = AXIS == 0 ? 1u : AXIS == 1 ? Gb : Gb * Gb;
   int best = at(i);
   for (int j = 1; j < best; ++j) {
-    int v = kNone;
+    int v = kMaxDist;
     if (c >= j) v = at(i - (uint32_t)j * pitch);
     if (c + j < (int)Gb) v = min(v, at(i + (uint32_t)j * pitch));
     best = min(best, max(j, v));
@@ -982,26 +1027,18 @@ hipError_t launch_render(const RenderArgs& a, int compute, int grid, int threads
   return hipGetLastError();
 }
 
-template <bool TAB16, int MODE, bool TET>
-static void launch_prune_impl(const FieldDev& F, float alpha, uint32_t npts, uint32_t p, const uint32_t* list,
-                              const uint32_t* count, uint32_t* bits_out, float* max_op, int n_cu, hipStream_t s) {
+template <bool TAB16, int MODE>
+static void launch_prune_mode(const FieldDev& F, float alpha, uint32_t npts, uint32_t p, uint32_t* bits_out,
+                              float* max_op, int n_cu, hipStream_t s) {
   static int per_cu = -1;
   if (per_cu < 0) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, prune_kernel<TAB16, MODE, TET>, kBlock, 0) !=
-            hipSuccess || nb < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, prune_kernel<TAB16, MODE>, kBlock, 0) != hipSuccess || nb < 1)
       nb = 1;
     per_cu = nb;
   }
-  hipLaunchKernelGGL((prune_kernel<TAB16, MODE, TET>), dim3((unsigned)(per_cu * n_cu)), dim3(kBlock), 0, s, F,
-                     alpha, npts, p, list, count, bits_out, max_op);
-}
-
-template <bool TAB16, int MODE>
-static void launch_prune_mode(const FieldDev& F, float alpha, uint32_t npts, uint32_t p, const uint32_t* list,
-                              const uint32_t* count, uint32_t* bits_out, float* max_op, int n_cu, hipStream_t s) {
-  if (npts == 4) launch_prune_impl<TAB16, MODE, true>(F, alpha, npts, p, list, count, bits_out, max_op, n_cu, s);
-  else launch_prune_impl<TAB16, MODE, false>(F, alpha, npts, p, list, count, bits_out, max_op, n_cu, s);
+  hipLaunchKernelGGL((prune_kernel<TAB16, MODE>), dim3((unsigned)(per_cu * n_cu)), dim3(kBlock), 0, s, F, alpha, npts,
+                     p, F.group_list, F.group_total, bits_out, max_op);
 }
 
 hipError_t launch_prune(const FieldDev& F, float alpha, uint32_t npts, int compute, uint32_t* bits_out,
@@ -1010,23 +1047,22 @@ hipError_t launch_prune(const FieldDev& F, float alpha, uint32_t npts, int compu
   while ((p + 1) * (p + 1) * (p + 1) <= npts) ++p;
   const uint32_t n = F.G * F.G * F.G;
   const uint32_t words = (n + 31u) / 32u;
-  hipLaunchKernelGGL(prune_init_kernel, dim3((words + 255u) / 256u), dim3(256), 0, s, F, bits_out, max_op);
-  hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s, F.brick_count, (uint64_t)1);
-  const uint32_t nb = F.Gb * F.Gb * F.Gb;
-  hipLaunchKernelGGL(brick_list_kernel, dim3((nb + 255u) / 256u), dim3(256), 0, s, F, F.brick_list,
-                     F.brick_count);
-  const uint32_t* list = F.brick_list;
-  const uint32_t* cnt = F.brick_count;
+  hipLaunchKernelGGL(prune_init_kernel, dim3((words + 255u) / 256u), dim3(256), 0, s, F, bits_out);
+  if (max_op) hipLaunchKernelGGL(nan_kernel, dim3(std::min((n + 255u) / 256u, (uint32_t)n_cu * 32u)), dim3(256), 0, s, max_op, (uint64_t)n);
+  hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s,
+                     reinterpret_cast<uint32_t*>(F.group_total), (uint64_t)2);
+  const uint32_t ng = (F.Gb + 3u) / 4u * F.Gb * F.Gb;
+  hipLaunchKernelGGL(group_list_kernel, dim3((ng + 255u) / 256u), dim3(256), 0, s, F, F.group_list, F.group_total);
   if (F.table_f16) {
-    if (compute == 0) launch_prune_mode<true, 0>(F, alpha, npts, p, list, cnt, bits_out, max_op, n_cu, s);
-    else if (compute == 1) launch_prune_mode<true, 1>(F, alpha, npts, p, list, cnt, bits_out, max_op, n_cu, s);
-    else if (compute == 3) launch_prune_mode<true, 3>(F, alpha, npts, p, list, cnt, bits_out, max_op, n_cu, s);
-    else launch_prune_mode<true, 2>(F, alpha, npts, p, list, cnt, bits_out, max_op, n_cu, s);
+    if (compute == 0) launch_prune_mode<true, 0>(F, alpha, npts, p, bits_out, max_op, n_cu, s);
+    else if (compute == 1) launch_prune_mode<true, 1>(F, alpha, npts, p, bits_out, max_op, n_cu, s);
+    else if (compute == 3) launch_prune_mode<true, 3>(F, alpha, npts, p, bits_out, max_op, n_cu, s);
+    else launch_prune_mode<true, 2>(F, alpha, npts, p, bits_out, max_op, n_cu, s);
   } else {
-    if (compute == 0) launch_prune_mode<false, 0>(F, alpha, npts, p, list, cnt, bits_out, max_op, n_cu, s);
-    else if (compute == 1) launch_prune_mode<false, 1>(F, alpha, npts, p, list, cnt, bits_out, max_op, n_cu, s);
-    else if (compute == 3) launch_prune_mode<false, 3>(F, alpha, npts, p, list, cnt, bits_out, max_op, n_cu, s);
-    else launch_prune_mode<false, 2>(F, alpha, npts, p, list, cnt, bits_out, max_op, n_cu, s);
+    if (compute == 0) launch_prune_mode<false, 0>(F, alpha, npts, p, bits_out, max_op, n_cu, s);
+    else if (compute == 1) launch_prune_mode<false, 1>(F, alpha, npts, p, bits_out, max_op, n_cu, s);
+    else if (compute == 3) launch_prune_mode<false, 3>(F, alpha, npts, p, bits_out, max_op, n_cu, s);
+    else launch_prune_mode<false, 2>(F, alpha, npts, p, bits_out, max_op, n_cu, s);
   }
   return hipGetLastError();
 }
@@ -1034,7 +1070,7 @@ hipError_t launch_prune(const FieldDev& F, float alpha, uint32_t npts, int compu
 hipError_t launch_brick_distance(const FieldDev& F, hipStream_t s) {
   const dim3 gr((F.Gb * F.Gb * F.Gb + 255u) / 256u), bl(256);
   uint8_t* d = const_cast<uint8_t*>(F.dist);
-  uint8_t* tmp = reinterpret_cast<uint8_t*>(F.brick_list);
+  uint8_t* tmp = reinterpret_cast<uint8_t*>(F.group_list);
   hipLaunchKernelGGL(brick_distance_kernel<0>, gr, bl, 0, s, F, nullptr, d);
   hipLaunchKernelGGL(brick_distance_kernel<1>, gr, bl, 0, s, F, d, tmp);
   hipLaunchKernelGGL(brick_distance_kernel<2>, gr, bl, 0, s, F, tmp, d);
