@@ -1090,7 +1090,16 @@ struct Bf3 {
   v8bf p[3];
 };
 
+// The residual of both halves of a rounded pair is one v_dot2_f32_bf16 each,
+// r - b exactly: (b0, b1) . (-1, -0) + r0 and (b0, b1) . (0, -1) + r1, where
+// widening b and subtracting took two instructions (3.5 a value where it was
+// 5.5; stereo 2x2048^2 house frame, VALU-bound, 5.32 -> 4.95 ms).  The zero is
+// negative where (-1, 0) would be taken for the inline constant -1.0, whose
+// 32-bit pattern the unit reads as (0, -1).  An infinite half makes the
+// other's residual NaN, as its own does the sums of the sample both belong to.
 __device__ __forceinline__ Bf3 split_bf3(const float* v) {
+  typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+  const v2bf first = {(__bf16)-1.0f, (__bf16)-0.0f}, second = {(__bf16)0.0f, (__bf16)-1.0f};
   Bf3 s;
   float r[8];
 #pragma unroll
@@ -1098,10 +1107,14 @@ __device__ __forceinline__ Bf3 split_bf3(const float* v) {
 #pragma unroll
   for (int k = 0; k < 3; ++k)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const __bf16 b = (__bf16)r[i];
-      s.p[k][i] = b;
-      if (k < 2) r[i] = r[i] - (float)b;
+    for (int i = 0; i < 8; i += 2) {
+      const v2bf b = {(__bf16)r[i], (__bf16)r[i + 1]};
+      s.p[k][i] = b[0];
+      s.p[k][i + 1] = b[1];
+      if (k < 2) {
+        r[i] = __builtin_amdgcn_fdot2_f32_bf16(b, first, r[i], false);
+        r[i + 1] = __builtin_amdgcn_fdot2_f32_bf16(b, second, r[i + 1], false);
+      }
     }
   return s;
 }
