@@ -840,7 +840,7 @@ vrn_status vrn_mlp(vrn_ctx* ctx, vrn_field_id field, const float* d_feat, const 
   if (n == 0) return VRN_OK;
   hipSetDevice(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_mlp(f->dev, d_feat, d_dir, n, (int)compute, d_sigma, d_rgb, s);
+  hipError_t e = launch_mlp(f->dev, d_feat, d_dir, n, (int)compute, d_sigma, d_rgb, ctx->n_cu, s);
   if (e != hipSuccess) return hip_fail(e, "mlp");
   track(f, s);
   return VRN_OK;

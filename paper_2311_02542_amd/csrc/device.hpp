@@ -719,6 +719,10 @@ __device__ __forceinline__ void sh_basis16(float x, float y, float z, float s[16
 __device__ __forceinline__ void sh_select(const FieldDev& F, float x, float y, float z, int g, float out[4]) {
   float s[16];
   sh_basis16(x, y, z, s);
+  // all values, then selects: left to itself the compiler branches on g and
+  // walks the four paths one after the other
+#pragma unroll
+  for (int i = 0; i < 16; ++i) asm("" : "+v"(s[i]));
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const float v = g == 0 ? s[4 * i] : g == 1 ? s[4 * i + 1] : g == 2 ? s[4 * i + 2] : s[4 * i + 3];
@@ -932,63 +936,6 @@ struct Half8 {
     else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
 };
-
-template <bool BF>
-__device__ __forceinline__ void mlp_tile_16(const uint4* __restrict__ sw, const float* __restrict__ sb,
-                                            const float feat[8], uint2 shh, int lane, float& o0, float lg[3]) {
-  typedef Half8<BF> H;
-  typedef typename H::vec vec;
-  const int g = lane >> 4;
-  auto wfrag = [&](int off16, int idx) -> vec {
-    const uint4 u = sw[off16 / 8 + idx * 64 + lane];
-    vec v;
-    __builtin_memcpy(&v, &u, 16);
-    return v;
-  };
-  const vec xin = H::pack(feat);
-  v4f h[4];
-#pragma unroll
-  for (int ot = 0; ot < 4; ++ot) h[ot] = add_bias4(H::mfma(wfrag(kW16_D1, ot), xin, zero4()), sb, kB1 + 16 * ot, g);
-  float hv[16];
-#pragma unroll
-  for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) hv[4 * ot + r] = h[ot][r];
-  v4f o = zero4();
-  o = H::mfma(wfrag(kW16_D2, 0), H::relu_pack(hv), o);
-  o = H::mfma(wfrag(kW16_D2, 1), H::relu_pack(hv + 8), o);
-  o = add_bias4(o, sb, kB2, g);
-  const float oo[4] = {o[0], o[1], o[2], o[3]};
-  const vec cv = H::pack4_raw(oo, shh);
-  v4f c1[4];
-#pragma unroll
-  for (int ot = 0; ot < 4; ++ot) c1[ot] = add_bias4(H::mfma(wfrag(kW16_C1, ot), cv, zero4()), sb, kB3 + 16 * ot, g);
-#pragma unroll
-  for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) hv[4 * ot + r] = c1[ot][r];
-  const vec a0 = H::relu_pack(hv), a1 = H::relu_pack(hv + 8);
-  v4f c2[4];
-#pragma unroll
-  for (int ot = 0; ot < 4; ++ot) {
-    c2[ot] = zero4();
-    c2[ot] = H::mfma(wfrag(kW16_C2, ot * 2 + 0), a0, c2[ot]);
-    c2[ot] = H::mfma(wfrag(kW16_C2, ot * 2 + 1), a1, c2[ot]);
-    c2[ot] = add_bias4(c2[ot], sb, kB4 + 16 * ot, g);
-  }
-#pragma unroll
-  for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) hv[4 * ot + r] = c2[ot][r];
-  v4f c3 = zero4();
-  c3 = H::mfma(wfrag(kW16_C3, 0), H::relu_pack(hv), c3);
-  c3 = H::mfma(wfrag(kW16_C3, 1), H::relu_pack(hv + 8), c3);
-  c3 = add_bias4(c3, sb, kB5, g);
-  o0 = o[0];
-  lg[0] = c3[0];
-  lg[1] = c3[1];
-  lg[2] = c3[2];
-}
 
 // The 16-bit MLPs over up to four 16-sample tiles at once: every weight
 // fragment is read from LDS once per call and applied to all tiles, so LDS

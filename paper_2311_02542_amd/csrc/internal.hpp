@@ -19,6 +19,7 @@ constexpr int kBlock = 256;         // threads per render block (4 waves)
 // allow.
 constexpr int kBlockF32 = 1024;
 inline int render_block_threads(int compute) { return (compute == 0 || compute == 3) ? kBlockF32 : kBlock; }
+constexpr int kMlpThreads = 512;   // most threads of a block of the MLP stage kernel
 constexpr int kHidden = 64;
 constexpr int kMaxDist = 16;        // longest brick distance held: one of 8 already takes the house scene's
                                     // march as far per ray to within 0.2 %
@@ -167,7 +168,7 @@ hipError_t launch_set_occupancy(const FieldDev& F, const uint32_t* bits, hipStre
 // The distance grid of the field's bricks (F.dist), with F.group_list as scratch.
 hipError_t launch_brick_distance(const FieldDev& F, hipStream_t s);
 hipError_t launch_mlp(const FieldDev& F, const float* feat, const float* dir, uint32_t n,
-                      int compute, float* sigma, float* rgb, hipStream_t s);
+                      int compute, float* sigma, float* rgb, int n_cu, hipStream_t s);
 
 // Shared by the C ABI (capi.cpp) with the serving engine (server.cpp).
 // set_error records vrn_last_error() for this thread and returns s.

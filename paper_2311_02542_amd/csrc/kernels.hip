@@ -122,9 +122,15 @@ __device__ __forceinline__ void run_mlp(const uint8_t* s_w, const float* s_b, co
   else if constexpr (MODE == 3)
     mlp_tile_x3(reinterpret_cast<const uint4*>(s_w), reinterpret_cast<const float4*>(s_w + kX3Bytes), s_b, feat,
                 shs, lane, o0, lg);
-  else
-    mlp_tile_16<MODE == 2>(reinterpret_cast<const uint4*>(s_w), s_b, feat, Half8<MODE == 2>::pack4(shs), lane,
-                           o0, lg);
+  else {
+    typedef Half8<MODE == 2> H;
+    const typename H::vec xin[1] = {H::pack(feat)};
+    const uint2 shh[1] = {H::pack4(shs)};
+    float o[1], l[1][3];
+    mlp_batch_16<MODE == 2, 1>(reinterpret_cast<const uint4*>(s_w), s_b, 1, xin, shh, lane, o, l);
+    o0 = o[0];
+    for (int c = 0; c < 3; ++c) lg[c] = l[0][c];
+  }
 }
 
 // The lane that owns compacted sample s = 16 t + (lane & 15), from the
@@ -569,31 +575,60 @@ __global__ __launch_bounds__(kBlock) void encode_kernel(FieldDev F, const float*
   }
 }
 
+// Blocks stay and walk the samples a tile a wave at a time, so that a block's
+// weights are staged once; a wave loads its next tile's inputs before it
+// evaluates the present one.  2 M samples of 16 levels, FP16: 183 us with a
+// block staging its weights for every 64 samples, 105 with resident blocks, 96
+// with the loads ahead, of which the reads and writes take 64 at the rate of a
+// copy and the LDS reads of weights and biases 58.  (Two tiles a wave halve
+// the latter, but at 82 registers fewer waves hide the loads: 133 us.  Blocks
+// of 256 and 1024 threads: 101 and 98.)  FP32X 487 -> 234 us; FP32 416 -> 338,
+// bound by its MFMA (245 us).
 template <int MODE>
-__global__ __launch_bounds__(kBlock) void mlp_kernel(FieldDev F, const float* feat, const float* dir,
-                                                     uint32_t n, float* sigma, float* rgb) {
+__global__ __launch_bounds__(kMlpThreads) void mlp_kernel(FieldDev F, const float* feat, const float* dir, uint32_t n,
+                                                          float* sigma, float* rgb) {
   __shared__ __align__(16) uint8_t s_w[WeightSmem<MODE>::kBytes];
   __shared__ float s_b[kBiasTotal];
   load_weights<MODE>(F, s_w, s_b);
   __syncthreads();
   const int lane = lane_id(), g = lane >> 4;
-  const uint64_t p = (blockIdx.x * (uint64_t)(kBlock / 64) + threadIdx.x / 64) * 16 + (lane & 15);
-  const bool act = p < n;
-  float f[8], shs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int e = 0; e < 8; ++e) {
-    const int lev = g + 4 * (e >> 1);
-    f[e] = (act && lev < (int)F.L) ? feat[p * (2 * F.L) + 2 * lev + (e & 1)] : 0.0f;
-  }
-  const float dx = act ? dir[3 * p] : 0.0f, dy = act ? dir[3 * p + 1] : 0.0f,
-              dz = act ? dir[3 * p + 2] : 0.0f;
-  sh_select(F, dx, dy, dz, g, shs);
-  float o0, lg[3];
-  run_mlp<MODE>(s_w, s_b, F, f, shs, lane, o0, lg);
-  if (act && g == 0) {
-    sigma[p] = expf(o0);
-    rgb[3 * p] = sigmoidf<false>(lg[0]);
-    rgb[3 * p + 1] = sigmoidf<false>(lg[1]);
-    rgb[3 * p + 2] = sigmoidf<false>(lg[2]);
+  const uint32_t tiles = (n + 15u) / 16u, wpb = blockDim.x / 64u;
+  float f[8], d[3];
+  auto load = [&](uint32_t t) {
+    const uint64_t p = (uint64_t)t * 16u + (uint32_t)(lane & 15);
+    const bool act = p < n;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int lev = g + 4 * j;
+      float2 v = make_float2(0.0f, 0.0f);
+      if (act && lev < (int)F.L) __builtin_memcpy(&v, feat + p * (2 * F.L) + 2 * lev, 8);   // 4-byte aligned
+      f[2 * j] = v.x;
+      f[2 * j + 1] = v.y;
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) d[a] = act ? dir[3 * p + a] : 0.0f;
+  };
+  uint32_t t = blockIdx.x * wpb + threadIdx.x / 64u;
+  if (t < tiles) load(t);
+  while (t < tiles) {
+    float shs[4], now[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) now[i] = f[i];
+    sh_select(F, d[0], d[1], d[2], g, shs);
+    const uint64_t p = (uint64_t)t * 16u + (uint32_t)(lane & 15);
+    t += gridDim.x * wpb;
+    if (t < tiles) load(t);
+    asm volatile("" ::: "memory");
+    float o0, lg[3];
+    run_mlp<MODE>(s_w, s_b, F, now, shs, lane, o0, lg);
+    // lanes 0..15 hold the results: one output a lane group, so that one
+    // library exponential serves all four
+    const float z0 = shfl_f(lg[0], lane & 15), z1 = shfl_f(lg[1], lane & 15), z2 = shfl_f(lg[2], lane & 15);
+    const float e = expf(g == 0 ? o0 : -(g == 1 ? z0 : g == 2 ? z1 : z2));
+    if (p < n) {
+      if (g == 0) sigma[p] = e;
+      else rgb[3 * p + (uint32_t)(g - 1)] = __builtin_amdgcn_rcpf(1.0f + e);
+    }
   }
 }
 
@@ -1186,14 +1221,29 @@ hipError_t launch_encode(const FieldDev& F, const float* xyz, const float* t, co
   return hipGetLastError();
 }
 
+template <int MODE>
+static void launch_mlp_mode(const FieldDev& F, const float* feat, const float* dir, uint32_t n, float* sigma, float* rgb,
+                            int n_cu, hipStream_t s) {
+  static int per_cu = -1;
+  if (per_cu < 0) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mlp_kernel<MODE>, kMlpThreads, 0) != hipSuccess || nb < 1)
+      nb = 1;
+    per_cu = nb;
+  }
+  // few waves: blocks of fewer of them (4 or more, for the staging) on more CUs
+  const uint32_t waves = (n + 15u) / 16u, most = kMlpThreads / 64;
+  const uint32_t wpb = std::min(most, std::max(4u, (waves + (uint32_t)n_cu - 1u) / (uint32_t)n_cu));
+  const uint32_t grid = std::min((waves + wpb - 1u) / wpb, (uint32_t)(n_cu * per_cu));
+  hipLaunchKernelGGL(mlp_kernel<MODE>, dim3(grid), dim3(wpb * 64u), 0, s, F, feat, dir, n, sigma, rgb);
+}
+
 hipError_t launch_mlp(const FieldDev& F, const float* feat, const float* dir, uint32_t n, int compute,
-                      float* sigma, float* rgb, hipStream_t s) {
-  const uint64_t per_block = (kBlock / 64) * 16;
-  const dim3 gr((unsigned)(((uint64_t)n + per_block - 1) / per_block)), bl(kBlock);
-  if (compute == 0) hipLaunchKernelGGL((mlp_kernel<0>), gr, bl, 0, s, F, feat, dir, n, sigma, rgb);
-  else if (compute == 1) hipLaunchKernelGGL((mlp_kernel<1>), gr, bl, 0, s, F, feat, dir, n, sigma, rgb);
-  else if (compute == 3) hipLaunchKernelGGL((mlp_kernel<3>), gr, bl, 0, s, F, feat, dir, n, sigma, rgb);
-  else hipLaunchKernelGGL((mlp_kernel<2>), gr, bl, 0, s, F, feat, dir, n, sigma, rgb);
+                      float* sigma, float* rgb, int n_cu, hipStream_t s) {
+  if (compute == 0) launch_mlp_mode<0>(F, feat, dir, n, sigma, rgb, n_cu, s);
+  else if (compute == 1) launch_mlp_mode<1>(F, feat, dir, n, sigma, rgb, n_cu, s);
+  else if (compute == 3) launch_mlp_mode<3>(F, feat, dir, n, sigma, rgb, n_cu, s);
+  else launch_mlp_mode<2>(F, feat, dir, n, sigma, rgb, n_cu, s);
   return hipGetLastError();
 }
 
