@@ -3,9 +3,10 @@
 // render_kernel is the whole per-ray path in one launch (the paper's
 // single-kernel interleave of ray marching, hash sampling and MLPs, Sec. 5):
 // persistent waves own 64 rays each (one per lane); every round a wave
-//   1. refills lanes whose ray finished from a per-XCD queue of 8x8 pixel
-//      tiles (XCD-aware: block b works the queue of XCD b % 8 first, whose
-//      tiles come in long runs, so each XCD's L2 sees coherent regions);
+//   1. takes the rays of the next 8x8 pixel tile when its own have all ended,
+//      from a per-XCD queue (XCD-aware: block b works the queue of XCD b % 8
+//      first, whose tiles come in long runs, so each XCD's L2 sees coherent
+//      regions);
 //   2. marches every ray to its next occupied lattice sample (bounded
 //      number of lattice tests per round, empty bricks skipped);
 //   3. compacts the lanes that found a sample into 16-sample tiles and, per
@@ -233,8 +234,8 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   // 64 runs a frame balance the queues, and still leave an XCD's L2 whole tile
   // rows of a large frame (shorter runs cost the 2x2048^2 house frame 1 %).  A
   // queue's ids count its own tiles' pixels: the first dealt(q) go to its
-  // blocks' waves by position, the rest as lanes fall free, and what is left
-  // of the next two queues then.  An atomic on a line that other XCDs share
+  // blocks' waves by position, the rest to waves whose rays have all ended, as
+  // does then what is left of the next two queues.  An atomic on a line that other XCDs share
   // takes some 20 ns, one after another: drawing every ray through them and
   // trying all eight queues at the end cost each launch 50-90 us (an empty
   // 512^2 frame 114 us, now 27).
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   const uint32_t size = ((((n_tiles + (1u << run) - 1u) >> run) + nq - 1u) / nq << run) * (kTile * kTile);
   auto dealt = [&](uint32_t i) { return (gridDim.x + nq - 1u - i) / nq * wpb * A.lanes; };
   uint32_t q = blockIdx.x % nq, tried = 0;
-  bool dealing = true, out_of_work = false;
+  bool dealing = true;
 
   Ray r;
   r.k = 0;
@@ -284,11 +285,13 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     // weights in registers and drop occupancy to one wave per SIMD)
     asm volatile("" ::: "memory");
     VRN_PHASE(kPhComposite);
-    // ---- 1. refill lanes that have no ray -------------------------------
-    while (!out_of_work) {
-      const bool open = pix == kNone && (uint32_t)lane < A.lanes;
-      const uint64_t need = __ballot(open);
-      if (need == 0) break;
+    // ---- 1. a wave whose rays have all ended takes the next ones ---------
+    // (The rays of a tile take nearly the same number of samples, so lanes
+    // filled one by one as they fell free gained no fuller MLP tiles, but one
+    // refill a ray's end instead of one a tile: stereo 2x2048^2 house frame
+    // 2.47 -> 2.37 ms, unbounded 1.88 -> 1.74, with thresholds of 16, 32, 48
+    // and 56 free lanes in between.)
+    while (__ballot(pix != kNone) == 0) {
       uint32_t base;
       if (dealing) {
         base = (blockIdx.x / nq * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * A.lanes;
@@ -297,43 +300,39 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
         base = dealt(q);
         uint32_t taken = 0;
         if (base < size) {
-          if (lane == 0) taken = atomicAdd(&queues[q].taken, (uint32_t)__popcll(need));
+          if (lane == 0) taken = atomicAdd(&queues[q].taken, A.lanes);
           base += (uint32_t)__builtin_amdgcn_readfirstlane((int)taken);
         }
-        if (base >= size) {
-          if (++tried > kHelped) out_of_work = true;
-          q = q + 1u == nq ? 0u : q + 1u;
-          continue;
-        }
       }
-      if (open) {
-        const uint32_t id = base + (uint32_t)__popcll(need & ((1ull << lane) - 1ull));
-        const uint32_t own = id / (kTile * kTile), within = id % (kTile * kTile);
-        const uint32_t turn = own >> run;
-        const uint32_t tile = ((turn * nq + ((q + turn) & (nq - 1u))) << run) + (own & ((1u << run) - 1u));
-        if (tile < n_tiles) {
-          uint32_t c = 0;
-          while (c + 1 < A.n_cams && tile >= s_off[c + 1]) ++c;
-          const uint32_t local = tile - s_off[c];
-          // local / tx without an integer division: float quotient, then an
-          // exact integer correction (local < 2^24)
-          uint32_t ty = (uint32_t)((float)local * inv_tx);
-          if (ty * tx > local) --ty;
-          else if ((ty + 1) * tx <= local) ++ty;
-          const uint32_t col = (local - ty * tx) * kTile + within % kTile;
-          const uint32_t row = s_rb[c] + ty * kTile + within / kTile;
-          if (col < A.W && row < s_re[c]) {
-            setup_ray<GEO>(F, A.cams[c], col, row, r);
-            if constexpr (!kF32Class<MODE>) store_ray_sh<MODE == 2>(F, r, &s_sh[threadIdx.x * 4]);
-            else store_ray_sh_f32(F, r, &s_sh4[threadIdx.x * 4]);
-            pix = (c * A.H + row) * A.W + col;
-            T = 1.0f;
-            cr = cg = cb = 0.0f;
-            n = 0;
-          }
-        }
+      if (base >= size) {
+        if (tried++ == kHelped) break;
+        q = q + 1u == nq ? 0u : q + 1u;
+        continue;
       }
-      st_rays += (uint32_t)__popcll(__ballot(open && pix != kNone));
+      const uint32_t own = base / (kTile * kTile), turn = own >> run;
+      const uint32_t tile = ((turn * nq + ((q + turn) & (nq - 1u))) << run) + (own & ((1u << run) - 1u));
+      if (tile >= n_tiles) continue;
+      uint32_t c = 0;
+      while (c + 1 < A.n_cams && tile >= s_off[c + 1]) ++c;
+      const uint32_t local = tile - s_off[c];
+      // local / tx without an integer division: float quotient, then an exact
+      // integer correction (local < 2^24)
+      uint32_t ty = (uint32_t)((float)local * inv_tx);
+      if (ty * tx > local) --ty;
+      else if ((ty + 1) * tx <= local) ++ty;
+      const uint32_t within = base % (kTile * kTile) + (uint32_t)lane;
+      const uint32_t col = (local - ty * tx) * kTile + within % kTile;
+      const uint32_t row = s_rb[c] + ty * kTile + within / kTile;
+      if ((uint32_t)lane < A.lanes && col < A.W && row < s_re[c]) {
+        setup_ray<GEO>(F, A.cams[c], col, row, r);
+        if constexpr (!kF32Class<MODE>) store_ray_sh<MODE == 2>(F, r, &s_sh[threadIdx.x * 4]);
+        else store_ray_sh_f32(F, r, &s_sh4[threadIdx.x * 4]);
+        pix = (c * A.H + row) * A.W + col;
+        T = 1.0f;
+        cr = cg = cb = 0.0f;
+        n = 0;
+      }
+      st_rays += (uint32_t)__popcll(__ballot(pix != kNone));
     }
     VRN_PHASE(kPhRefill);
     if (__ballot(pix != kNone) == 0) break;
