@@ -140,6 +140,7 @@ struct SSlot {
   hipEvent_t ev = nullptr;
   std::map<Key, std::vector<OutBuf*>> rings;
   std::vector<SReq*> busy;  // the launch in flight
+  uint64_t launched = 0;    // the server's launch count at the slot's last one
 };
 
 }  // namespace
@@ -288,14 +289,38 @@ void finish(vrn_server* sv, SReq* r, int32_t status, double t) {
   else sv->counts.failed += 1;
 }
 
+// The idle slot for a launch of key: one with a free buffer (and its graph),
+// else the one idle for longest, where a new buffer is captured.  The first
+// idle slot, as it was, captured again where a request had ended and its
+// result was still held, with the other slots' buffers free: a 256^2 FP16
+// request took 85 to 130 us instead of 70.
+SSlot* idle_slot(vrn_server* sv, const Key& key) {
+  SSlot* best = nullptr;
+  bool best_ready = false;
+  for (SSlot& s : sv->slots) {
+    if (!s.busy.empty()) continue;
+    bool ready = false;
+    const auto it = s.rings.find(key);
+    if (it != s.rings.end())
+      for (const OutBuf* o : it->second) ready = ready || o->holders == 0;
+    if (!best || (ready && !best_ready) || (ready == best_ready && s.launched < best->launched)) {
+      best = &s;
+      best_ready = ready;
+    }
+  }
+  return best;
+}
+
 // 1: the batch was launched (or failed for good); 0: its output buffer does
-// not fit the arena now.
-int launch(vrn_server* sv, SSlot& slot, const std::vector<SReq*>& batch) {
+// not fit the arena now.  A slot is idle.
+int launch(vrn_server* sv, const std::vector<SReq*>& batch) {
   const SReq* r0 = batch[0];
   uint32_t n = 0;
   for (const SReq* r : batch) n += r->n_cams;
   OutBuf* o = nullptr;
-  const vrn_status st = acquire_out(sv, slot, Key(r0->field, r0->W, r0->H, n), &o);
+  const Key key(r0->field, r0->W, r0->H, n);
+  SSlot& slot = *idle_slot(sv, key);
+  const vrn_status st = acquire_out(sv, slot, key, &o);
   if (st == VRN_ERR_BUDGET) return 0;
   if (st != VRN_OK) {
     const double t = now_s();
@@ -337,6 +362,7 @@ int launch(vrn_server* sv, SSlot& slot, const std::vector<SReq*>& batch) {
   }
   slot.busy = batch;
   sv->counts.launches += 1;
+  slot.launched = sv->counts.launches;
   if (o->exec) sv->counts.graph_launches += 1;
   sv->counts.merged_requests += batch.size() - 1;
   return 1;
@@ -415,23 +441,18 @@ void loop(vrn_server* sv) {
     expire(sv);
     bool launched = false;
     if (!sv->hold && !sv->pending.empty()) {
-      SSlot* free_slot = nullptr;
       size_t n_free = 0;
-      for (SSlot& s : sv->slots)
-        if (s.busy.empty()) {
-          ++n_free;
-          if (!free_slot) free_slot = &s;
-        }
-      if (free_slot) {
+      for (const SSlot& s : sv->slots) n_free += s.busy.empty();
+      if (n_free) {
         const std::vector<SReq*> batch = take_batch(sv);
-        if (launch(sv, *free_slot, batch)) {
+        if (launch(sv, batch)) {
           launched = true;
         } else if (n_free == sv->slots.size()) {
           // nothing in flight will free memory: shrink to the head request;
           // if even that does not fit it waits for held results to be
           // released, and fails only when none are held
           requeue(sv, batch, 1);
-          if (launch(sv, *free_slot, {batch[0]})) {
+          if (launch(sv, {batch[0]})) {
             launched = true;
           } else if (held_bytes(sv) > 0) {
             sv->pending.push_front(batch[0]);
