@@ -101,16 +101,28 @@ __device__ __forceinline__ const uint4* weight_src(const FieldDev& F) {
   else return reinterpret_cast<const uint4*>(F.wx3);
 }
 
+// Copy n 16-byte words to LDS with a block of any size, eight loads a thread in
+// flight: with one, the 20 to 70 of a small launch's one-wave blocks came one
+// after the other (256^2 FP16 frame 76 -> 67 us, together with the end of
+// launches whose rays are all dealt).
+__device__ __forceinline__ void stage(uint4* dst, const uint4* __restrict__ src, uint32_t n) {
+  for (uint32_t i = threadIdx.x; i < n; i += 8u * blockDim.x) {
+    uint4 v[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8u; ++k) v[k] = src[min(i + k * blockDim.x, n - 1u)];
+#pragma unroll
+    for (uint32_t k = 0; k < 8u; ++k)
+      if (i + k * blockDim.x < n) dst[i + k * blockDim.x] = v[k];
+  }
+}
+
 template <int MODE>
 __device__ __forceinline__ void load_weights(const FieldDev& F, uint8_t* s_w, float* s_b) {
-  const uint4* src = weight_src<MODE>(F);
   uint4* dst = reinterpret_cast<uint4*>(s_w);
   constexpr int kMain = MODE == 3 ? kX3Bytes : WeightSmem<MODE>::kBytes;
-  for (int i = threadIdx.x; i < kMain / 16; i += blockDim.x) dst[i] = src[i];
-  if constexpr (MODE == 3) {
-    const uint4* c3 = reinterpret_cast<const uint4*>(F.w32 + kW32_C3);
-    for (int i = threadIdx.x; i < (kW32Total - kW32_C3) / 4; i += blockDim.x) dst[kX3Bytes / 16 + i] = c3[i];
-  }
+  stage(dst, weight_src<MODE>(F), kMain / 16);
+  if constexpr (MODE == 3)
+    stage(dst + kX3Bytes / 16, reinterpret_cast<const uint4*>(F.w32 + kW32_C3), (kW32Total - kW32_C3) / 4);
   for (int i = threadIdx.x; i < kBiasTotal; i += blockDim.x) s_b[i] = F.bias[i];
 }
 
@@ -204,26 +216,36 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   uint2* s_sh = reinterpret_cast<uint2*>(s_sh_raw);
   float4* s_sh4 = reinterpret_cast<float4*>(s_sh_raw);
   __shared__ uint32_t s_slot[kThreads];
+  // the FP32-class kernels keep their rays' steps per cell here between
+  // marches: their registers run out (FP32X spilled 8, now 6)
+  __shared__ float s_iq[kF32Class<MODE> ? 3 * kThreads : 1];
 
   const FieldDev& F = A.F;
   const __amdgpu_buffer_rsrc_t tab = table_rsrc(F);
-  load_weights<MODE>(F, s_w, s_b);
   if (threadIdx.x < F.L) s_lv[threadIdx.x] = F.levels[threadIdx.x];
   if (threadIdx.x < kStats) s_stats[threadIdx.x] = 0;
   const uint32_t tx = (A.W + kTile - 1) / kTile;
   const float inv_tx = 1.0f / (float)tx;
-  if (threadIdx.x == 0) {
-    uint32_t acc = 0;
-    for (uint32_t c = 0; c < A.n_cams; ++c) {
-      const uint32_t rb = min(A.cams[c].row_begin, A.H);
-      const uint32_t re = min(max(A.cams[c].row_end, rb), A.H);
-      s_off[c] = acc;
-      s_rb[c] = rb;
-      s_re[c] = re;
-      acc += tx * ((re - rb + kTile - 1) / kTile);
+  if (threadIdx.x < 64) {
+    // camera c's first tile: an inclusive scan over the first 16 lanes
+    uint32_t own = 0;
+    if (threadIdx.x < A.n_cams) {
+      const vrn_camera& cam = A.cams[threadIdx.x];
+      const uint32_t rb = min(cam.row_begin, A.H), re = min(max(cam.row_end, rb), A.H);
+      s_rb[threadIdx.x] = rb;
+      s_re[threadIdx.x] = re;
+      own = tx * ((re - rb + kTile - 1) / kTile);
     }
-    s_off[A.n_cams] = acc;
+    uint32_t upto = own;
+#pragma unroll
+    for (int d = 1; d < kMaxCams; d *= 2) {
+      const uint32_t o = (uint32_t)shfl_i((int)upto, lane_id() - d);
+      if (lane_id() >= d) upto += o;
+    }
+    if (threadIdx.x < A.n_cams) s_off[threadIdx.x + 1] = upto;
+    if (threadIdx.x == 0) s_off[0] = 0;
   }
+  load_weights<MODE>(F, s_w, s_b);
   __syncthreads();
 
   const int lane = lane_id();
@@ -325,6 +347,10 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
       const uint32_t row = s_rb[c] + ty * kTile + within / kTile;
       if ((uint32_t)lane < A.lanes && col < A.W && row < s_re[c]) {
         setup_ray<GEO>(F, A.cams[c], col, row, r);
+        if constexpr (kF32Class<MODE>) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) s_iq[a * kThreads + threadIdx.x] = r.iq[a];
+        }
         if constexpr (!kF32Class<MODE>) store_ray_sh<MODE == 2>(F, r, &s_sh[threadIdx.x * 4]);
         else store_ray_sh_f32(F, r, &s_sh4[threadIdx.x * 4]);
         pix = (c * A.H + row) * A.W + col;
@@ -342,6 +368,10 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     int mres = 0;
     float st = 0.0f, sx[3] = {0.0f, 0.0f, 0.0f}, slst = 0.0f, sdt = F.dt;
     if (pix != kNone) {
+      if constexpr (kF32Class<MODE>) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) r.iq[a] = s_iq[a * kThreads + threadIdx.x];
+      }
       mres = march_next<GEO>(F, r, A.budget, st_steps, st, sx);
       if (mres == 2) retire();
       if (mres == 1) {
@@ -473,6 +503,13 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     atomicAdd(&s_stats[5], st_tiles);
   }
   __syncthreads();
+  if (dealt(nq - 1u) >= size) {
+    // no queue was touched (a small launch): nothing to reset, only to count
+    if (threadIdx.x < kStats)
+      atomicAdd(reinterpret_cast<unsigned long long*>(A.ws + kWsStats) + threadIdx.x,
+                (unsigned long long)s_stats[threadIdx.x]);
+    return;
+  }
   // Statistics and the count of finished blocks gather on the line of the
   // block's own queue, six lanes at once; its last block counts the queue as
   // finished, and the last of those adds the queues' sums up and leaves every
