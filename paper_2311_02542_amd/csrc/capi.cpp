@@ -325,12 +325,15 @@ vrn_status check_opts(const vrn_render_opts* opts) {
   return VRN_OK;
 }
 
-vrn_status do_render(vrn_ctx* ctx, Field* f, const vrn_camera* d_cams, uint32_t n_cams, uint32_t W,
-                     uint32_t H, const vrn_render_opts* opts, float* d_rgba, uint32_t* d_nsamples, void* ws,
-                     hipStream_t s, bool noalloc = false) {
+// The cameras are d_cams in device memory, or else h_cams on the host, which
+// go with the launch.
+vrn_status do_render(vrn_ctx* ctx, Field* f, const vrn_camera* d_cams, const vrn_camera* h_cams, uint32_t n_cams,
+                     uint32_t W, uint32_t H, const vrn_render_opts* opts, float* d_rgba, uint32_t* d_nsamples,
+                     void* ws, hipStream_t s, bool noalloc = false) {
   RenderArgs a{};
   a.F = f->dev;
   a.cams = d_cams;
+  if (!d_cams) std::memcpy(a.own_cams, h_cams, n_cams * sizeof(vrn_camera));
   a.n_cams = n_cams;
   a.W = W;
   a.H = H;
@@ -705,14 +708,17 @@ static vrn_status render_common(vrn_ctx* ctx, vrn_field_id field, const vrn_came
   if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
   void* w = ws ? ws : ctx->ws;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const vrn_camera* d_cams = cams;
-  if (!cams_dev) {
+  // Host cameras are kernel arguments.  A captured render keeps its copy: a
+  // replay reads the host memory anew.
+  const vrn_camera* d_cams = cams_dev ? cams : nullptr;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (!cams_dev && (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) {
     uint8_t* slot = static_cast<uint8_t*>(w) + kWsCams;
     e = hipMemcpyAsync(slot, cams, n_cams * sizeof(vrn_camera), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "camera upload");
     d_cams = reinterpret_cast<const vrn_camera*>(slot);
   }
-  return do_render(ctx, f, d_cams, n_cams, W, H, opts, d_rgba, d_nsamples, w, s);
+  return do_render(ctx, f, d_cams, cams, n_cams, W, H, opts, d_rgba, d_nsamples, w, s);
 }
 
 vrn_status vrn_render(vrn_ctx* ctx, vrn_field_id field, const vrn_camera* cams, uint32_t n_cams, uint32_t W,
@@ -752,7 +758,7 @@ vrn_status vrn_render_noalloc(vrn_ctx* ctx, vrn_field_id field, const vrn_camera
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   // counters start at zero: a fill kernel, not a memset (safe under capture)
   if ((e = launch_zero(ctx->scratch, kScratchBytes, s)) != hipSuccess) return hip_fail(e, "scratch clear");
-  return do_render(ctx, f, d_cams, n_cams, W, H, opts, d_rgba, d_nsamples, ctx->scratch, s, true);
+  return do_render(ctx, f, d_cams, nullptr, n_cams, W, H, opts, d_rgba, d_nsamples, ctx->scratch, s, true);
 }
 
 vrn_status vrn_read_stats(vrn_ctx* ctx, const void* ws, vrn_stats* out, void* stream) {

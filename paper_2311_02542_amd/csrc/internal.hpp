@@ -111,7 +111,7 @@ static_assert(kScratchBytes >= kWsCams, "scratch holds every counter of a worksp
 
 struct RenderArgs {
   FieldDev F;
-  const vrn_camera* cams;    // device
+  const vrn_camera* cams;    // device; null: own_cams
   uint32_t n_cams, W, H;
   float* rgba;               // [n_cams][H][W][4]
   uint32_t* nsamples;        // nullable
@@ -120,6 +120,7 @@ struct RenderArgs {
   float exposure;            // 2^exposure_ev (VRN_OUT_SRGB)
   uint32_t budget;           // march steps per round
   uint32_t lanes;            // rays a wave carries at once: its first 16, 32 or all 64 lanes
+  vrn_camera own_cams[kMaxCams];
 };
 
 // launchers (kernels.hip)

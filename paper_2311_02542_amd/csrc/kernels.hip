@@ -210,6 +210,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   __shared__ LevelDev s_lv[kMaxLevels];
   __shared__ uint32_t s_off[kMaxCams + 1];
   __shared__ uint32_t s_rb[kMaxCams], s_re[kMaxCams];
+  __shared__ vrn_camera s_cams[kMaxCams];
   __shared__ uint32_t s_stats[kStats];
   // per-ray SH values: FP32 [lane][g] float4 (FP32 path) or packed 16-bit [lane][g] uint2
   __shared__ __align__(16) uint8_t s_sh_raw[kThreads * 4 * (kF32Class<MODE> ? 16 : 8)];
@@ -226,12 +227,27 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   if (threadIdx.x < kStats) s_stats[threadIdx.x] = 0;
   const uint32_t tx = (A.W + kTile - 1) / kTile;
   const float inv_tx = 1.0f / (float)tx;
+  // The cameras, from the caller's device memory or from the kernel's own
+  // arguments, in words (the caller's need not be aligned to more).  In the
+  // arguments they cost no copy ahead of the kernel (256^2 FP16 frame 66 ->
+  // 63 us), and rays are set up from LDS (2x2048^2 FP32X house 5100 -> 5065).
+  typedef const __attribute__((address_space(1))) uint32_t* GlobalWords;
+  constexpr uint32_t kCamWords = sizeof(vrn_camera) / 4;
+  const GlobalWords cams = (GlobalWords)(A.cams ? reinterpret_cast<uint64_t>(A.cams)
+                                                : (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() +
+                                                      offsetof(RenderArgs, own_cams));
+  uint32_t row_begin = 0, row_end = 0;
+  if (threadIdx.x < A.n_cams) {
+    row_begin = cams[threadIdx.x * kCamWords + offsetof(vrn_camera, row_begin) / 4];
+    row_end = cams[threadIdx.x * kCamWords + offsetof(vrn_camera, row_end) / 4];
+  }
+  for (uint32_t i = threadIdx.x; i < A.n_cams * kCamWords; i += blockDim.x)
+    reinterpret_cast<uint32_t*>(s_cams)[i] = cams[i];
   if (threadIdx.x < 64) {
     // camera c's first tile: an inclusive scan over the first 16 lanes
     uint32_t own = 0;
     if (threadIdx.x < A.n_cams) {
-      const vrn_camera& cam = A.cams[threadIdx.x];
-      const uint32_t rb = min(cam.row_begin, A.H), re = min(max(cam.row_end, rb), A.H);
+      const uint32_t rb = min(row_begin, A.H), re = min(max(row_end, rb), A.H);
       s_rb[threadIdx.x] = rb;
       s_re[threadIdx.x] = re;
       own = tx * ((re - rb + kTile - 1) / kTile);
@@ -346,7 +362,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
       const uint32_t col = (local - ty * tx) * kTile + within % kTile;
       const uint32_t row = s_rb[c] + ty * kTile + within / kTile;
       if ((uint32_t)lane < A.lanes && col < A.W && row < s_re[c]) {
-        setup_ray<GEO>(F, A.cams[c], col, row, r);
+        setup_ray<GEO>(F, s_cams[c], col, row, r);
         if constexpr (kF32Class<MODE>) {
 #pragma unroll
           for (int a = 0; a < 3; ++a) s_iq[a * kThreads + threadIdx.x] = r.iq[a];
