@@ -358,7 +358,13 @@ vrn_status do_render(vrn_ctx* ctx, Field* f, const vrn_camera* d_cams, const vrn
   const uint64_t waves = (rays + a.lanes - 1) / a.lanes;
   const uint64_t per_block = std::min(block_waves, (waves + ctx->n_cu - 1) / ctx->n_cu);
   const int grid = (int)std::min((waves + per_block - 1) / per_block, blocks);
-  hipError_t e = launch_render(a, compute, grid, (int)per_block * 64, s);
+  // Blocks of few waves get more (up to 8 in all) that carry no rays and only
+  // help to copy the weights: one wave took five turns of eight loads over the
+  // FP32 weights (64^2 FP32 frame 33.5 us, with 4, 8 and 16 waves 29.1, 28.5
+  // and 28.5; the 256^2 FP16 frame has no block this small).
+  a.waves = (uint32_t)per_block;
+  const uint64_t threads = 64 * std::min(block_waves, std::max<uint64_t>(per_block, 8));
+  hipError_t e = launch_render(a, compute, grid, (int)threads, s);
   if (e != hipSuccess) return hip_fail(e, "render launch");
   if (!noalloc) {
     track(f, s);

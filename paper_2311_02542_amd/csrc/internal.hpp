@@ -120,6 +120,7 @@ struct RenderArgs {
   float exposure;            // 2^exposure_ev (VRN_OUT_SRGB)
   uint32_t budget;           // march steps per round
   uint32_t lanes;            // rays a wave carries at once: its first 16, 32 or all 64 lanes
+  uint32_t waves;            // waves of a block that carry rays; others only help to copy weights
   vrn_camera own_cams[kMaxCams];
 };
 

@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   float4* s_sh4 = reinterpret_cast<float4*>(s_sh_raw);
   __shared__ uint32_t s_slot[kThreads];
   // the FP32-class kernels keep their rays' steps per cell here between
-  // marches: their registers run out (FP32X spilled 8, now 6)
+  // marches: their registers run out (FP32X spilled 8, now 2)
   __shared__ float s_iq[kF32Class<MODE> ? 3 * kThreads : 1];
 
   const FieldDev& F = A.F;
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   // takes some 20 ns, one after another: drawing every ray through them and
   // trying all eight queues at the end cost each launch 50-90 us (an empty
   // 512^2 frame 114 us, now 27).
-  const uint32_t nq = gridDim.x >= (uint32_t)kQueues ? (uint32_t)kQueues : 1u, wpb = blockDim.x >> 6;
+  const uint32_t nq = gridDim.x >= (uint32_t)kQueues ? (uint32_t)kQueues : 1u, wpb = A.waves;
   const uint32_t run = n_tiles < 128u ? 0u : 25u - (uint32_t)__clz((int)n_tiles);
   const uint32_t size = ((((n_tiles + (1u << run) - 1u) >> run) + nq - 1u) / nq << run) * (kTile * kTile);
   auto dealt = [&](uint32_t i) { return (gridDim.x + nq - 1u - i) / nq * wpb * A.lanes; };
@@ -318,7 +318,8 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     pix = kNone;
   };
 
-  while (true) {
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  while (wave < wpb) {
     // keep LDS reads of weights inside the loop (hoisting would pin the
     // weights in registers and drop occupancy to one wave per SIMD)
     asm volatile("" ::: "memory");
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     while (__ballot(pix != kNone) == 0) {
       uint32_t base;
       if (dealing) {
-        base = (blockIdx.x / nq * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * A.lanes;
+        base = (blockIdx.x / nq * wpb + wave) * A.lanes;
         dealing = false;
       } else {
         base = dealt(q);
