@@ -218,8 +218,11 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
   float4* s_sh4 = reinterpret_cast<float4*>(s_sh_raw);
   __shared__ uint32_t s_slot[kThreads];
   // the FP32-class kernels keep their rays' steps per cell here between
-  // marches: their registers run out (FP32X spilled 8, now 2)
-  __shared__ float s_iq[kF32Class<MODE> ? 3 * kThreads : 1];
+  // marches, and with a sample table the neighbour pixel's direction (only a
+  // found sample's LOD reads it): their registers run out (FP32X spilled 8 and
+  // 19, now 2 and 14; 1024^2 unbounded frame 555 -> 527 us.  One more value of
+  // the uniform lattice's rays changed nothing)
+  __shared__ float s_ray[kF32Class<MODE> ? (GEO == 1 ? 6 : 3) * kThreads : 1];
 
   const FieldDev& F = A.F;
   const __amdgpu_buffer_rsrc_t tab = table_rsrc(F);
@@ -366,7 +369,12 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
         setup_ray<GEO>(F, s_cams[c], col, row, r);
         if constexpr (kF32Class<MODE>) {
 #pragma unroll
-          for (int a = 0; a < 3; ++a) s_iq[a * kThreads + threadIdx.x] = r.iq[a];
+          for (int a = 0; a < 3; ++a) s_ray[a * kThreads + threadIdx.x] = r.iq[a];
+          if constexpr (GEO == 1) {
+            s_ray[3 * kThreads + threadIdx.x] = r.nx;
+            s_ray[4 * kThreads + threadIdx.x] = r.ny;
+            s_ray[5 * kThreads + threadIdx.x] = r.nz;
+          }
         }
         if constexpr (!kF32Class<MODE>) store_ray_sh<MODE == 2>(F, r, &s_sh[threadIdx.x * 4]);
         else store_ray_sh_f32(F, r, &s_sh4[threadIdx.x * 4]);
@@ -387,11 +395,16 @@ __global__ __launch_bounds__(kF32Class<MODE> ? kBlockF32 : kBlock, kF32Class<MOD
     if (pix != kNone) {
       if constexpr (kF32Class<MODE>) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) r.iq[a] = s_iq[a * kThreads + threadIdx.x];
+        for (int a = 0; a < 3; ++a) r.iq[a] = s_ray[a * kThreads + threadIdx.x];
       }
       mres = march_next<GEO>(F, r, A.budget, st_steps, st, sx);
       if (mres == 2) retire();
       if (mres == 1) {
+        if constexpr (kF32Class<MODE> && GEO == 1) {
+          r.nx = s_ray[3 * kThreads + threadIdx.x];
+          r.ny = s_ray[4 * kThreads + threadIdx.x];
+          r.nz = s_ray[5 * kThreads + threadIdx.x];
+        }
         if (F.lod) slst = (GEO == 1 && F.contract) ? level_star_contracted(F, r, st, sx) : level_star(F, st, r.lr);
         sdt = sample_step<GEO>(F, st);
       }
