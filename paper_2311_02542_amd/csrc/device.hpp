@@ -42,7 +42,7 @@ struct Ray {
   int brick;     // index of the 4x4x4 brick cached below (-1: none)
   int dist;      // its distance to the nearest non-empty brick (0: non-empty)
   uint32_t blo, bhi;  // its bits, when it is non-empty
-  float iq[3];   // lattice steps (sample tables: ray parameter) per cell along each axis, finite
+  float iq[3];   // lattice steps (sample tables: ray parameter) per cell along each axis (no motion: infinite)
   float nx, ny, nz;  // right neighbour's direction (contracted LOD footprint)
 };
 
@@ -204,13 +204,10 @@ __device__ __forceinline__ void setup_ray(const FieldDev& F, const vrn_camera& c
   r.dist = 0;
   r.blo = r.bhi = 0u;
   lattice_range<GEO>(F, r);
-  // (hardware reciprocals: skip_straight's margin covers their ~1 ulp)
+  // (hardware reciprocals: the margin of exit_steps covers their ~1 ulp)
   const float per = GEO == 0 ? F.cs * F.dt : (F.contract ? F.inv_radius * F.cs : F.cs);
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const float inv = __builtin_amdgcn_rcpf(d[a] * per);
-    r.iq[a] = copysignf(fminf(fabsf(inv), 1.0e30f), d[a]);
-  }
+  for (int a = 0; a < 3; ++a) r.iq[a] = __builtin_amdgcn_rcpf(d[a] * per);
 }
 
 // ---------------------------------------------------------------------------
@@ -290,17 +287,22 @@ __device__ __forceinline__ uint32_t grid_index(uint32_t x, uint32_t y, uint32_t 
 }
 
 // Lattice steps (sample tables: ray parameter) from the current sample to the
-// exit of an empty box, less a margin; 0 where the sample is too near a face.
-// The box holds the sample's cell c (q its canonical position): an empty cell
-// of a non-empty brick alone, or the bricks nearer than dist to an empty one,
-// which hold no occupied cell (beyond the grid nothing is occupied).  Only
-// the faces towards which the ray moves matter.  Along an axis the exact ray
-// advances 1 / iq cells a step and canonical positions stray from it by at
-// most delta / 2, so of the samples up to the exit from the box shrunk by mu =
-// 2 delta none has a canonical cell beyond a far face: the second delta covers
-// the rounding of this evaluation, a few ulp of G.  None falls behind a near
-// face either when the sample lies delta or more inside its cell; within
-// delta of a face (one sample in a hundred) no skip is made.
+// exit of an empty box, less a margin.  The box holds the sample's cell c (q
+// its canonical position): an empty cell of a non-empty brick alone, or the
+// bricks nearer than dist to an empty one, which hold no occupied cell (beyond
+// the grid nothing is occupied).  Only the faces towards which the ray moves
+// matter: every operation of a canonical position rounds monotonically, so
+// along an axis the positions of later samples never fall behind q.  The exact
+// ray advances 1 / iq cells a step and canonical positions stray from it by at
+// most delta / 2, so of the samples up to the exit from the box shrunk by 2
+// delta none has a canonical cell beyond a far face: the second delta covers
+// the rounding of this evaluation, a few ulp of G.  An axis without motion
+// (iq infinite) bounds nothing: its term is an infinity less an infinity, or
+// zero times one, and fminf leaves a NaN out.  A ray along a plane of the grid
+// skips like its neighbours.  (Asking every sample for a distance of delta from
+// the faces of its cell, and taking the near face for a component of +0, made
+// such a ray test every sample: a level 256x255 house frame, whose middle row
+// has d_z = +0, took 603 us, and takes 100 now.)
 // face_lo and face_hi bound the faces (identity region of contracted fields).
 template <bool CLAMP>
 __device__ __forceinline__ float exit_steps(const Ray& r, const float q[3], const int c[3], float face_lo,
@@ -308,17 +310,14 @@ __device__ __forceinline__ float exit_steps(const Ray& r, const float q[3], cons
   const bool full = r.dist != 0;       // empty brick
   const int sh = full ? 2 : 0;
   const int up = full ? r.dist : 1, dn = 1 - up;
-  const float d[3] = {r.dx, r.dy, r.dz};
-  float n[3], inside = 0.0f;
+  float n[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    float face = (float)(((c[a] >> sh) + (d[a] > 0.0f ? up : dn)) << sh);
+    float face = (float)(((c[a] >> sh) + (r.iq[a] > 0.0f ? up : dn)) << sh);
     if constexpr (CLAMP) face = fminf(fmaxf(face, face_lo), face_hi);
     n[a] = fmaf(fabsf(r.iq[a]), -2.0f * r.delta, (face - q[a]) * r.iq[a]);
-    inside = fmaxf(inside, fabsf(__builtin_amdgcn_fractf(q[a]) - 0.5f));
   }
-  const float m = fminf(n[0], fminf(n[1], n[2]));
-  return inside <= 0.5f - r.delta ? m : 0.0f;
+  return fminf(n[0], fminf(n[1], n[2]));
 }
 
 // Largest index whose table entry is certainly <= t (-1: none is certain):
@@ -437,12 +436,13 @@ __device__ __forceinline__ int march_next(const FieldDev& F, Ray& r, uint32_t bu
       const float n = exit_steps<false>(r, q, c, 0.0f, 0.0f);
       next += (int)__builtin_amdgcn_fmed3f(inside ? n : 0.0f, 0.0f, 16777216.0f);
     } else if (inside) {
-      // inside the unit ball (q in [G/4, 3G/4]) C is the identity
+      // inside the unit ball (q in [G/4, 3G/4]) C is the identity; within
+      // delta of its faces positions may be those of either side: no skip
       const float lo = 0.25f * (float)F.G, hi = 0.75f * (float)F.G;
+      const float in = fminf(fminf(q[0], fminf(q[1], q[2])) - lo, hi - fmaxf(q[0], fmaxf(q[1], q[2])));
       float n;
       if (!F.contract) n = exit_steps<false>(r, q, c, 0.0f, 0.0f);
-      else if (fminf(q[0], fminf(q[1], q[2])) >= lo && fmaxf(q[0], fmaxf(q[1], q[2])) <= hi)
-        n = exit_steps<true>(r, q, c, lo, hi);
+      else if (in >= 0.0f) n = in >= r.delta ? exit_steps<true>(r, q, c, lo, hi) : 0.0f;
       else n = exit_curved(F, r, t, q, c);
       // (the exit's rounding, an ulp of t, is far inside the margin)
       if (n > 0.0f) next = max(next, min(table_floor(F, t + n), r.k_hi) + 1);
