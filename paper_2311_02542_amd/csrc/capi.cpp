@@ -298,9 +298,18 @@ void free_field(Field* f) {
   delete f;
 }
 
-void track(Field* f, hipStream_t s) {
+// Whether s records a graph.  A query that fails (the null stream beside the
+// capture of a blocking one) counts as yes; its error is cleared, because
+// launches report the thread's last one.
+bool capturing(hipStream_t s) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return;
+  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+void track(Field* f, hipStream_t s) {
+  if (capturing(s)) return;
   hipEvent_t ev = nullptr;
   for (hipEvent_t e : f->events)
     if (hipEventQuery(e) == hipSuccess) {
@@ -366,13 +375,8 @@ vrn_status do_render(vrn_ctx* ctx, Field* f, const vrn_camera* d_cams, const vrn
   const uint64_t threads = 64 * std::min(block_waves, std::max<uint64_t>(per_block, 8));
   hipError_t e = launch_render(a, compute, grid, (int)threads, s);
   if (e != hipSuccess) return hip_fail(e, "render launch");
-  if (!noalloc) {
-    track(f, s);
-  } else {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone)
-      hipEventRecord(f->noalloc_ev, s);
-  }
+  if (!noalloc) track(f, s);
+  else if (!capturing(s)) hipEventRecord(f->noalloc_ev, s);
   return VRN_OK;
 }
 
@@ -717,8 +721,7 @@ static vrn_status render_common(vrn_ctx* ctx, vrn_field_id field, const vrn_came
   // Host cameras are kernel arguments.  A captured render keeps its copy: a
   // replay reads the host memory anew.
   const vrn_camera* d_cams = cams_dev ? cams : nullptr;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (!cams_dev && (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) {
+  if (!cams_dev && capturing(s)) {
     uint8_t* slot = static_cast<uint8_t*>(w) + kWsCams;
     e = hipMemcpyAsync(slot, cams, n_cams * sizeof(vrn_camera), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "camera upload");
