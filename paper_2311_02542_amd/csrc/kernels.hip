@@ -1168,21 +1168,26 @@ hipError_t launch_prune(const FieldDev& F, float alpha, uint32_t npts, int compu
   return hipGetLastError();
 }
 
+// Launched through the calls that return a launch's own status: the thread's
+// last error may be another call's, and loading a field does not fail for it.
 hipError_t launch_brick_distance(const FieldDev& F, hipStream_t s) {
   const dim3 gr((F.Gb * F.Gb * F.Gb + 255u) / 256u), bl(256);
-  uint8_t* d = const_cast<uint8_t*>(F.dist);
-  uint8_t* tmp = reinterpret_cast<uint8_t*>(F.group_list);
-  hipLaunchKernelGGL(brick_distance_kernel<0>, gr, bl, 0, s, F, nullptr, d);
-  hipLaunchKernelGGL(brick_distance_kernel<1>, gr, bl, 0, s, F, d, tmp);
-  hipLaunchKernelGGL(brick_distance_kernel<2>, gr, bl, 0, s, F, tmp, d);
-  return hipGetLastError();
+  FieldDev f = F;
+  uint8_t *d = const_cast<uint8_t*>(F.dist), *tmp = reinterpret_cast<uint8_t*>(F.group_list);
+  const uint8_t *none = nullptr, *from_d = d, *from_tmp = tmp;
+  void *x[] = {&f, &none, &d}, *y[] = {&f, &from_d, &tmp}, *z[] = {&f, &from_tmp, &d};
+  hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&brick_distance_kernel<0>), gr, bl, x, 0, s);
+  if (e == hipSuccess) e = hipLaunchKernel(reinterpret_cast<const void*>(&brick_distance_kernel<1>), gr, bl, y, 0, s);
+  if (e == hipSuccess) e = hipLaunchKernel(reinterpret_cast<const void*>(&brick_distance_kernel<2>), gr, bl, z, 0, s);
+  return e;
 }
 
 hipError_t launch_set_occupancy(const FieldDev& F, const uint32_t* bits, hipStream_t s) {
   const uint64_t nb = (uint64_t)F.Gb * F.Gb * F.Gb;
   hipLaunchKernelGGL(bricks_from_bits_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, F,
                      const_cast<unsigned long long*>(F.bricks), bits);
-  return launch_brick_distance(F, s);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_brick_distance(F, s) : e;
 }
 
 hipError_t phase_cycles(unsigned long long out[kPhaseSlots], bool reset) {

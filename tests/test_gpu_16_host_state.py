@@ -50,3 +50,13 @@ def test_host_cameras_on_the_null_stream_beside_a_capture(R, mode):
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and int(want[1].sum()) > 0
     assert hip.hipGraphDestroy(graph) == 0 and hip.hipStreamDestroy(stream) == 0
     R.unload(fid)
+
+
+def test_load_after_another_call_has_failed(R):
+    R.torch.cuda.synchronize()
+    assert _hip().hipSetDevice(1 << 20) != 0          # leaves its error as the thread's last one
+    fid = R.load(synth.field_blobs64())
+    _hip().hipGetLastError()
+    cams = synth.cameras_blobs64(1, N, N)
+    assert int(R.render(fid, cams, N, N, "f32")[1].sum()) > 0
+    R.unload(fid)
