@@ -287,14 +287,17 @@ vrn_status vrn_mlp(vrn_ctx* ctx, vrn_field_id field, const float* d_feat, const 
  * 1 - exp(-sigma_max dt) >= alpha.  Pruning only clears bits.
  *   d_bits_out     device, ceil(G^3 / 32) uint32 words, bit i = x + G*(y + G*z).
  *   d_max_opacity  device [G^3] float (NaN for unoccupied voxels) or NULL.
- * The resident field is not modified (see vrn_set_occupancy). */
+ * The field's occupancy is not modified (see vrn_set_occupancy).  Pruning
+ * and occupancy calls of one field share scratch memory: each waits on the
+ * device for the one before it, whatever their streams.  Replays of captured
+ * ones must not overlap with each other or with such calls. */
 vrn_status vrn_prune_grid(vrn_ctx* ctx, vrn_field_id field, float alpha, uint32_t points_per_voxel,
                           vrn_dtype compute, uint32_t* d_bits_out, float* d_max_opacity, void* hip_stream);
 
 /* Replace a resident field's occupancy grid (Sec. 4.3) with device bits (same layout as
  * vrn_field_desc.occ_bits), rebuilding its bricks and their distances on
  * hip_stream.  Renders of this field on other streams must be ordered by
- * the caller. */
+ * the caller; pruning calls are ordered as vrn_prune_grid says. */
 vrn_status vrn_set_occupancy(vrn_ctx* ctx, vrn_field_id field, const uint32_t* d_bits, void* hip_stream);
 
 /* ---- serving engine: continuous batching of render requests ----

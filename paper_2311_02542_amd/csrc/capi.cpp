@@ -69,6 +69,8 @@ struct Field {
   // at load time and re-recorded by every such render (those renders share
   // one scratch array, so the caller serialises them on the device)
   hipEvent_t noalloc_ev = nullptr;
+  // pruning and occupancy calls in flight, see with_scratch
+  hipEvent_t scratch_ev = nullptr;
   // output buffers of serving engines whose graphs render this field
   int pins = 0;
 };
@@ -294,6 +296,7 @@ hipError_t alloc_only(Field* f, size_t count, T** out) {
 void free_field(Field* f) {
   for (hipEvent_t ev : f->events) hipEventDestroy(ev);
   if (f->noalloc_ev) hipEventDestroy(f->noalloc_ev);
+  if (f->scratch_ev) hipEventDestroy(f->scratch_ev);
   for (void* p : f->allocs) hipFree(p);
   delete f;
 }
@@ -321,6 +324,22 @@ void track(Field* f, hipStream_t s) {
     f->events.push_back(ev);
   }
   hipEventRecord(ev, s);
+}
+
+// Launches of vrn_prune_grid and vrn_set_occupancy: both write the field's
+// pruning list (the latter as scratch of the brick distances), and the one
+// reads the bricks that the other writes, so each waits for the one before it,
+// whatever their streams.  One event, re-recorded by each, therefore also
+// stands for all of them in flight.  Calls that record into a graph cannot
+// wait; their replays are the caller's to order.
+template <typename Launch>
+hipError_t with_scratch(Field* f, hipStream_t s, Launch launch) {
+  if (capturing(s)) return launch();
+  hipError_t e = hipStreamWaitEvent(s, f->scratch_ev, 0);
+  if (e != hipSuccess) return e;
+  e = launch();
+  const hipError_t r = hipEventRecord(f->scratch_ev, s);   // also after a launch that failed half way
+  return e == hipSuccess ? r : e;
 }
 
 vrn_status check_opts(const vrn_render_opts* opts) {
@@ -546,7 +565,8 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
       (e = upload(f, bias.data(), bias.size(), &dbias)) ||
       (use_table && (e = upload(f, lat.data(), lat.size(), &dlat))) ||
       (e = alloc_only(f, bricks.size(), &ddist)) || (e = alloc_only(f, (size_t)n_groups, &dlist)) || (e = upload(f, zeros.data(), zeros.size(), &dcount)) ||
-      (e = hipEventCreateWithFlags(&f->noalloc_ev, hipEventDisableTiming))) {
+      (e = hipEventCreateWithFlags(&f->noalloc_ev, hipEventDisableTiming)) ||
+      (e = hipEventCreateWithFlags(&f->scratch_ev, hipEventDisableTiming))) {
     free_field(f);
     return e == hipErrorOutOfMemory ? fail(VRN_ERR_OUT_OF_MEMORY, "device allocation failed")
                                     : hip_fail(e, "field upload");
@@ -644,7 +664,8 @@ vrn_status vrn_unload_field(vrn_ctx* ctx, vrn_field_id field) {
   hipSetDevice(ctx->device);
   for (hipEvent_t ev : f->events)
     if (hipEventQuery(ev) == hipErrorNotReady) return fail(VRN_ERR_BUSY, "field has renders in flight");
-  if (hipEventQuery(f->noalloc_ev) == hipErrorNotReady) return fail(VRN_ERR_BUSY, "field has renders in flight");
+  for (hipEvent_t ev : {f->noalloc_ev, f->scratch_ev})
+    if (hipEventQuery(ev) == hipErrorNotReady) return fail(VRN_ERR_BUSY, "field has renders in flight");
   if (f->pins > 0) return fail(VRN_ERR_BUSY, "a serving engine holds output buffers of this field");
   ctx->used -= f->bytes;
   ctx->fields.erase(field);
@@ -876,9 +897,10 @@ vrn_status vrn_prune_grid(vrn_ctx* ctx, vrn_field_id field, float alpha, uint32_
   if (!f) return fail(VRN_ERR_NOT_FOUND, "unknown field id");
   hipSetDevice(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_prune(f->dev, alpha, points_per_voxel, (int)compute, d_bits_out, d_max_opacity, ctx->n_cu, s);
+  hipError_t e = with_scratch(f, s, [&] {
+    return launch_prune(f->dev, alpha, points_per_voxel, (int)compute, d_bits_out, d_max_opacity, ctx->n_cu, s);
+  });
   if (e != hipSuccess) return hip_fail(e, "prune");
-  track(f, s);
   return VRN_OK;
 }
 
@@ -916,9 +938,8 @@ vrn_status vrn_set_occupancy(vrn_ctx* ctx, vrn_field_id field, const uint32_t* d
   if (!f) return fail(VRN_ERR_NOT_FOUND, "unknown field id");
   hipSetDevice(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_set_occupancy(f->dev, d_bits, s);
+  hipError_t e = with_scratch(f, s, [&] { return launch_set_occupancy(f->dev, d_bits, s); });
   if (e != hipSuccess) return hip_fail(e, "set occupancy");
-  track(f, s);
   return VRN_OK;
 }
 

@@ -789,7 +789,8 @@ __global__ void nan_kernel(float* p, uint64_t n) {
 // (2) the non-empty groups of four bricks along x, nearly in order: x the
 // index gx + ngx (by + Gb bz) with ngx = ceil(Gb / 4), y the number of
 // occupied voxels of the groups listed before.  total (zeroed before): groups
-// in the high word, voxels in the low one.
+// in the high word, voxels in the low one.  (Two replayed passes that run at
+// once may count every group twice: no slot beyond the list is written.)
 __global__ void group_list_kernel(FieldDev F, uint2* list, unsigned long long* total) {
   const uint32_t ngx = (F.Gb + 3u) / 4u, n = ngx * F.Gb * F.Gb;
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -811,7 +812,8 @@ __global__ void group_list_kernel(FieldDev F, uint2* list, unsigned long long* t
   if (lane == 63) base = atomicAdd(total, (unsigned long long)__popcll(m) << 32 | upto);
   const uint32_t entry = (uint32_t)__builtin_amdgcn_readlane((int)(base >> 32), 63);
   const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)base, 63);
-  if (voxels != 0u) list[entry + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = make_uint2(i, before + upto - voxels);
+  const uint32_t slot = entry + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+  if (voxels != 0u && slot < n) list[slot] = make_uint2(i, before + upto - voxels);
 }
 
 // Density layers only (the pruning pass needs sigma, not color), in the
@@ -902,7 +904,9 @@ struct DensitySmem {
 
 constexpr uint32_t kPruneChunk = 16;   // voxels a wave takes at once
 
-// (3) persistent pruning waves over the group list.
+// (3) persistent pruning waves over the group list.  The list is the field's,
+// not the call's: where replayed calls on one field overlap it may hold
+// anything, so nothing taken from it reaches an address unchecked.
 template <bool TAB16, int MODE>
 __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, uint32_t npts, uint32_t p,
                                                       const uint2* list, const unsigned long long* total,
@@ -931,13 +935,14 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
   // Each XCD takes an eighth of the voxels, in list order, and its waves one
   // chunk of it after the other side by side, so that neighbours meet in one L2.
   const uint32_t nx = gridDim.x >= (uint32_t)kQueues ? (uint32_t)kQueues : 1u, xcd = blockIdx.x % nx;
-  const uint32_t n_list = (uint32_t)(*total >> 32), n_vox = (uint32_t)*total;
+  const uint32_t G = F.G, Gb = F.Gb, ngx = (Gb + 3u) / 4u, n_groups = ngx * Gb * Gb;
+  const unsigned long long totals = *total;
+  const uint32_t n_list = min((uint32_t)(totals >> 32), n_groups), n_vox = min((uint32_t)totals, G * G * G);
   const uint32_t stop = (uint32_t)((uint64_t)n_vox * (xcd + 1u) / nx);
   const uint32_t stride = (gridDim.x + nx - 1u - xcd) / nx * (kBlock / 64) * kPruneChunk;
   // p points along x of a voxel (p^3 patterns) stand side by side in a tile
   const uint32_t sx = npts == 4u ? 1u : p, vpt = 16u / sx;
   const uint32_t vl = ((uint32_t)lane & 15u) / sx, px = ((uint32_t)lane & 15u) - vl * sx;
-  const uint32_t G = F.G, Gb = F.Gb, ngx = (Gb + 3u) / 4u;
   const float cell = F.inv_cs;
   for (uint32_t begin = (uint32_t)((uint64_t)n_vox * xcd / nx) +
                         (blockIdx.x / nx * (kBlock / 64) + (uint32_t)wv) * kPruneChunk;
@@ -949,9 +954,11 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
       if (list[mid].y <= begin) i = mid;
       else hi = mid;
     }
-    for (; i < n_list; ++i) {
+    if (lane < (int)kPruneChunk) q[lane] = kNone;
+    // (every group holds a voxel: a chunk meets no more groups than it has voxels)
+    for (const uint32_t past = min(i + kPruneChunk, n_list); i < past; ++i) {
       const uint2 entry = list[i];
-      if (entry.y >= end) break;
+      if (entry.y >= end || entry.x >= n_groups) break;
       // queue the occupied voxels of one group, rows of 16 along x one after
       // another, packed x | y << 10 | z << 20; lane 4 r + j holds row r of
       // brick j
@@ -976,8 +983,8 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
     const int V = (int)(end - begin);
     for (int t = 0; t < V; t += (int)vpt) {
       const int vr = t + (int)vl;
-      const bool act = vl < vpt && vr < V;
-      const uint32_t c = q[act ? vr : 0];
+      const uint32_t c = q[vl < vpt && vr < V ? vr : 0];
+      const bool act = vl < vpt && vr < V && c != kNone;
       const uint32_t cc[3] = {c & 1023u, (c >> 10) & 1023u, c >> 20};
       float most = 0.0f;
       for (uint32_t pi = px; pi < npts; pi += sx) {
