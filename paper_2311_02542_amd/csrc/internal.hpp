@@ -20,6 +20,21 @@ constexpr int kBlock = 256;         // threads per render block (4 waves)
 constexpr int kBlockF32 = 1024;
 inline int render_block_threads(int compute) { return (compute == 0 || compute == 3) ? kBlockF32 : kBlock; }
 constexpr int kMlpThreads = 512;   // most threads of a block of the MLP stage kernel
+
+// The MLP stage kernel's tiles of 16 samples, for any 32-bit count of them, and
+// its launch: at most the blocks that fit the chip; few tiles go to blocks of
+// fewer waves (4 or more, for the copy of the weights) on more CUs.
+constexpr uint32_t mlp_tiles(uint32_t n) { return n / 16u + (n % 16u != 0u ? 1u : 0u); }
+struct MlpShape {
+  uint32_t grid, threads;
+};
+constexpr MlpShape mlp_shape(uint32_t n, uint32_t n_cu, uint32_t blocks_per_cu) {
+  const uint32_t tiles = mlp_tiles(n), most = kMlpThreads / 64;
+  const uint32_t share = (tiles + n_cu - 1u) / n_cu, few = share < 4u ? 4u : share, wpb = few < most ? few : most;
+  const uint32_t want = (tiles + wpb - 1u) / wpb, fit = n_cu * blocks_per_cu;
+  return {want < fit ? want : fit, wpb * 64u};
+}
+
 constexpr int kHidden = 64;
 constexpr int kMaxDist = 16;        // longest brick distance held: one of 8 already takes the house scene's
                                     // march as far per ray to within 0.2 %

@@ -658,7 +658,7 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_kernel(FieldDev F, const floa
   load_weights<MODE>(F, s_w, s_b);
   __syncthreads();
   const int lane = lane_id(), g = lane >> 4;
-  const uint32_t tiles = (n + 15u) / 16u, wpb = blockDim.x / 64u;
+  const uint32_t tiles = mlp_tiles(n), wpb = blockDim.x / 64u;
   float f[8], d[3];
   auto load = [&](uint32_t t) {
     const uint64_t p = (uint64_t)t * 16u + (uint32_t)(lane & 15);
@@ -1309,11 +1309,8 @@ static void launch_mlp_mode(const FieldDev& F, const float* feat, const float* d
       nb = 1;
     per_cu = nb;
   }
-  // few waves: blocks of fewer of them (4 or more, for the staging) on more CUs
-  const uint32_t waves = (n + 15u) / 16u, most = kMlpThreads / 64;
-  const uint32_t wpb = std::min(most, std::max(4u, (waves + (uint32_t)n_cu - 1u) / (uint32_t)n_cu));
-  const uint32_t grid = std::min((waves + wpb - 1u) / wpb, (uint32_t)(n_cu * per_cu));
-  hipLaunchKernelGGL(mlp_kernel<MODE>, dim3(grid), dim3(wpb * 64u), 0, s, F, feat, dir, n, sigma, rgb);
+  const MlpShape shape = mlp_shape(n, (uint32_t)n_cu, (uint32_t)per_cu);
+  hipLaunchKernelGGL(mlp_kernel<MODE>, dim3(shape.grid), dim3(shape.threads), 0, s, F, feat, dir, n, sigma, rgb);
 }
 
 hipError_t launch_mlp(const FieldDev& F, const float* feat, const float* dir, uint32_t n, int compute,
