@@ -719,7 +719,7 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_kernel(FieldDev F, const floa
 // shares lines is neighbours along x and, on the coarser levels, all
 // neighbours, if they are looked up at about the same time: the L2 has room
 // for some 40 lines a wave.  A tile is therefore the same point of up to 16
-// voxels along x, and the waves of an XCD take neighbouring chunks of 16 side
+// voxels along x, where they form runs, and the waves of an XCD take neighbouring chunks of 16 side
 // by side.  FP16, 4 points: 6.40 ms with whole bricks dealt to the waves of all
 // XCDs in turn and four points of four voxels a tile, 6.05 ms with one
 // contiguous share a wave, 5.72, 5.60 and 5.40 ms with chunks of 64, 32 and 16
@@ -902,7 +902,7 @@ struct DensitySmem {
   static constexpr int kBytes = (MODE == 0) ? kW32_C1 * 4 : (MODE == 3 ? 3 * kW16_C1 * 2 : kW16_C1 * 2);
 };
 
-constexpr uint32_t kPruneChunk = 16;   // voxels a wave takes at once
+constexpr uint32_t kPruneChunk = 16;   // most voxels a wave takes at once
 
 // (3) persistent pruning waves over the group list.  The list is the field's,
 // not the call's: where replayed calls on one field overlap it may hold
@@ -930,7 +930,7 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
   }
   __syncthreads();
   const __amdgpu_buffer_rsrc_t tab = table_rsrc(F);
-  const int lane = lane_id(), g = lane >> 4, wv = threadIdx.x >> 6;
+  const int lane = lane_id(), g = lane >> 4, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint32_t* q = s_q[wv];
   // Each XCD takes an eighth of the voxels, in list order, and its waves one
   // chunk of it after the other side by side, so that neighbours meet in one L2.
@@ -938,16 +938,17 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
   const uint32_t G = F.G, Gb = F.Gb, ngx = (Gb + 3u) / 4u, n_groups = ngx * Gb * Gb;
   const unsigned long long totals = *total;
   const uint32_t n_list = min((uint32_t)(totals >> 32), n_groups), n_vox = min((uint32_t)totals, G * G * G);
-  const uint32_t stop = (uint32_t)((uint64_t)n_vox * (xcd + 1u) / nx);
-  const uint32_t stride = (gridDim.x + nx - 1u - xcd) / nx * (kBlock / 64) * kPruneChunk;
-  // p points along x of a voxel (p^3 patterns) stand side by side in a tile
-  const uint32_t sx = npts == 4u ? 1u : p, vpt = 16u / sx;
-  const uint32_t vl = ((uint32_t)lane & 15u) / sx, px = ((uint32_t)lane & 15u) - vl * sx;
+  const uint32_t start = (uint32_t)((uint64_t)n_vox * xcd / nx), stop = (uint32_t)((uint64_t)n_vox * (xcd + 1u) / nx);
+  const uint32_t waves = (gridDim.x + nx - 1u - xcd) / nx * (kBlock / 64), share = (stop - start + waves - 1u) / waves;
+  // A wave takes 16 voxels at once; where there are fewer for each, so many that
+  // every wave has some, in whole tiles of a run (100 voxels of 64 points on
+  // seven of 6144 waves 200 us, on a hundred 44; 10,000 of 4 points 99 and 84).
+  const uint32_t row = npts == 4u ? 1u : p, full = 16u / row;
+  const uint32_t chunk = share <= full ? max(share, 1u) : share <= 2u * full ? min(2u * full, kPruneChunk) : kPruneChunk;
+  const uint32_t stride = waves * chunk;
   const float cell = F.inv_cs;
-  for (uint32_t begin = (uint32_t)((uint64_t)n_vox * xcd / nx) +
-                        (blockIdx.x / nx * (kBlock / 64) + (uint32_t)wv) * kPruneChunk;
-       begin < stop; begin += stride) {
-    const uint32_t end = min(begin + kPruneChunk, stop);
+  for (uint32_t begin = start + (blockIdx.x / nx * (kBlock / 64) + (uint32_t)wv) * chunk; begin < stop; begin += stride) {
+    const uint32_t end = min(begin + chunk, stop);
     uint32_t i = 0;                     // the last entry that starts at or before begin
     for (uint32_t hi = n_list; hi - i > 1u;) {
       const uint32_t mid = i + (hi - i) / 2u;
@@ -980,22 +981,36 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
         }
     }
     __builtin_amdgcn_wave_barrier();
+    // How many points of a voxel stand side by side in a tile: of runs of voxels
+    // along x one, or the p along x of p^3 patterns, so that the voxels of a run
+    // meet; of voxels apart from each other (runs of 1.25 or less, where the two
+    // measure the same), and where a small chunk leaves lanes free, as many as
+    // fit.  4 points: planes across x 612 -> 555 us, along x 322 with one point
+    // and 380 with four; 120,000 scattered voxels 564 -> 490; the 256^3 room
+    // 1100 -> 998.
     const int V = (int)(end - begin);
+    const uint64_t joined = __ballot(lane > 0 && lane < V && q[lane & 15] == q[(lane - 1) & 15] + 1u);
+    const bool apart = 5u * (uint32_t)__popcll(joined) <= (uint32_t)V;
+    const uint32_t side = min(npts, apart ? 16u : max(row, 16u / (uint32_t)V));
+    const uint32_t vpt = 16u / side;
+    const uint32_t vl = ((uint32_t)lane & 15u) / side, px = ((uint32_t)lane & 15u) - vl * side;
     for (int t = 0; t < V; t += (int)vpt) {
       const int vr = t + (int)vl;
       const uint32_t c = q[vl < vpt && vr < V ? vr : 0];
       const bool act = vl < vpt && vr < V && c != kNone;
       const uint32_t cc[3] = {c & 1023u, (c >> 10) & 1023u, c >> 20};
       float most = 0.0f;
-      for (uint32_t pi = px; pi < npts; pi += sx) {
+      // (all lanes take every turn: a matrix product reads its weights from all)
+      for (uint32_t first = 0; first < npts; first += side) {
         asm volatile("" ::: "memory");
+        const uint32_t pi = first + px;
         float x[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) x[a] = F.amin[a] + ((float)cc[a] + voxel_offset(npts, p, pi, a)) * cell;
         float feat[8];
         uint32_t fetches = 0;
         // every level weighs 1 (no ray, no LOD): L* above the finest level
-        encode_point<TAB16, kF32Class<MODE>>(F, s_lv, tab, x, 1.0e9f, act, g, feat, fetches);
+        encode_point<TAB16, kF32Class<MODE>>(F, s_lv, tab, x, 1.0e9f, act && pi < npts, g, feat, fetches);
         float o0;
         if constexpr (MODE == 0)
           o0 = density_tile_f32(reinterpret_cast<const float4*>(s_w), s_b, F.d1_ksteps / 4, feat, lane);
@@ -1006,10 +1021,10 @@ __global__ __launch_bounds__(kBlock) void prune_kernel(FieldDev F, float alpha, 
         float op = 1.0f - expf(-expf(o0) * F.dt);
         // a NaN opacity (16-bit activations that overflowed) keeps the voxel
         if (!(op == op)) op = 1.0f;
-        most = fmaxf(most, op);
+        if (pi < npts) most = fmaxf(most, op);
       }
       float top = most;
-      for (uint32_t k = 1; k < sx; ++k) top = fmaxf(top, shfl_f(most, lane + (int)k));
+      for (uint32_t k = 1; k < side; ++k) top = fmaxf(top, shfl_f(most, lane + (int)k));
       if (act && g == 0 && px == 0u) {
         const uint32_t idx = cc[0] + G * (cc[1] + G * cc[2]);
         if (!(top >= alpha)) atomicAnd(&bits_out[idx >> 5], ~(1u << (idx & 31u)));
