@@ -197,7 +197,9 @@ vrn_status vrn_workspace_init(vrn_ctx* ctx, void* d_workspace, uint64_t workspac
  * compositing with early termination into PQ color (Sec. 4.1, Eq. 1-2), all
  * in one kernel launch (the single-kernel interleave of Sec. 5).
  *   cams        host [n_cams]; validated (finite, det(R) != 0, fx, fy > 0,
- *               row_begin < row_end <= H); copied into the workspace.
+ *               row_begin < row_end <= H).  Read before the call returns;
+ *               in a stream capture validated then, and copied into the
+ *               workspace from the same memory by every replay.
  *   d_rgba      device [n_cams][H][W][4] float: PQ (or linear) RGB, alpha = 1 - T.
  *   d_nsamples  device [n_cams][H][W] uint32 evaluated samples per pixel, or NULL.
  *   d_workspace device, >= vrn_workspace_bytes, initialised once by

@@ -402,6 +402,7 @@ def vrn_prune_grid(ctx, fid, alpha, bits_out, max_opacity=None, points_per_voxel
                               _ptr(max_opacity), _stream(stream)), lib)
 
 
+# (coarse_index, the header's unused slot, counts nothing: 0)
 DEBUG_SLOTS = ("table_offset", "brick_index", "coarse_index", "pixel_write", "nan_feature", "nan_mlp_output")
 
 

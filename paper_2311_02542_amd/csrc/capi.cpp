@@ -638,7 +638,6 @@ vrn_status vrn_load_field(vrn_ctx* ctx, const vrn_field_desc* d, vrn_field_id* o
   }
   F.contract = d->contraction;
   for (int a = 0; a < 3; ++a) F.center[a] = d->center[a];
-  F.radius = d->contraction ? d->radius : 1.0f;
   F.inv_radius = d->contraction ? (float)(1.0 / (double)d->radius) : 1.0f;
   F.lod_c2 = d->lod_enable ? (float)std::log(2.0 * (double)d->base_res) : 0.0f;
   F.dense_mask = 0;

@@ -82,8 +82,8 @@ __device__ __forceinline__ float cone_pitch(const vrn_camera& c, const float w[3
 // (1 + g) per step -- that the FP32 recurrence departs from by a fraction
 // of a step on the tables used here; a walk over neighbouring entries (two
 // independent loads per step) makes it exact, and a binary search takes
-// over if the walk runs long.  The plain binary search costs ~log2 K
-// dependent loads on every skip of the march.
+// over if the walk runs long.  The ends of a ray's range are found with it (a
+// plain binary search costs ~log2 K dependent loads); skips use table_floor.
 __device__ __forceinline__ int table_count_le(const FieldDev& F, float t) {
   const int K = (int)F.lat_K;
   if (!(t >= F.lat[0])) return 0;   // NaN included
@@ -384,9 +384,9 @@ __device__ __forceinline__ float exit_curved(const FieldDev& F, const Ray& r, fl
 // (exit_steps), so it pays even for a cell that holds a single further sample.
 // Bound by VALU issue and the latency of the chain from test to test: before,
 // a coarse grid in LDS with walks of its clear runs and single-box skips,
-// each re-testing where it landed, took 20.1 tests a ray on the stereo 2x2048^2
-// house frame (16-bit paths 2.87 ms) and 28 within the unbounded scene's room
-// (2.35-4.0 ms by pose); this takes 13.4 (2.48 ms) and 9.5 (1.27-1.86 ms).
+// each re-testing where it landed, took 20.7 tests a ray on the stereo 2x2048^2
+// house frame (16-bit paths 2.85 ms) and 31.5 on the unbounded scene's (2.4 to
+// 4.0 ms by pose); this takes 13.2 (2.35 ms) and 12.7 (1.2 to 1.7).
 // Both loads are issued at once: the bits only after a distance of 0 ran
 // 0.8 % slower on the house frame.
 // Beyond the unit ball of a contracted field samples follow a curve, along
